@@ -279,7 +279,7 @@ void set_timed(fb::PlanDeviceLaunch& a, const fb_cost_model& m, const int32_t* r
 // workgroup when it serves the plan; any other plan follows as a kernel of its own on the stream.
 int predict_then_plan(fb::PredictLaunch& a, const fb::PlanDeviceLaunch& p, size_t workspace_bytes) {
   const size_t sb = fb::split_workspace_bytes(a.T, a.E, a.H, a.dtype, a.num_cus);
-  if (sb > 0 && workspace_bytes >= fb::kWsBytes + sb) {
+  if (sb > 0 && workspace_bytes > fb::kWsBytes) {
     a.partial = reinterpret_cast<float*>(static_cast<char*>(a.workspace) + fb::kWsBytes);
     a.partial_bytes = workspace_bytes - fb::kWsBytes;
   }
@@ -335,9 +335,9 @@ int fb_predict_load_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_
   fb::PredictLaunch a = make_launch(hidden, T, H, ld_hidden, dtype, router_packed, E, logit_bias,
                                     select_bias, scoring, expert_to_rank, R, counts, rank_loads,
                                     max_mean, workspace, topk_idx, logits, stream);
-  // split mode when the caller's workspace holds the partial logits this batch needs
+  // split mode, in as many splits as the caller's workspace holds the partial logits of
   const size_t sb = fb::split_workspace_bytes(T, E, H, dtype, a.num_cus);
-  if (sb > 0 && workspace_bytes >= fb::kWsBytes + sb) {
+  if (sb > 0 && workspace_bytes > fb::kWsBytes) {
     a.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + fb::kWsBytes);
     a.partial_bytes = workspace_bytes - fb::kWsBytes;
   }

@@ -55,6 +55,7 @@ constexpr int kStepBytes = 32;                  // bytes of a row feeding one MF
 constexpr int kNStep = 8;                       // k-steps per stage
 constexpr int kStageRowBytes = kStepBytes * kNStep;   // 256
 constexpr int kRingW = 16;                      // router-weight k-step slices held per wave
+constexpr int kMaxSplits = 16;                  // workgroups that share a tile's stages
 constexpr int kMaxK = FB_MAX_TOPK;
 constexpr int kMaxGroups = 32;
 constexpr uint32_t kRsrcWord3 = 0x00020000u;    // raw buffer, 32-bit dwords
@@ -93,15 +94,15 @@ struct Params {
   double* max_mean;
   int32_t* ws_acc;
   uint32_t* ws_ticket;
-  uint32_t* ws_tile;   // split mode: arrivals per tile (kSplit)
+  uint32_t* ws_tile;   // split mode: arrival word per tile (kSplit)
   int32_t* topk_idx;
   float* logits;
-  uint32_t nblocks;
+  uint32_t nblocks;    // workgroups of the launch, and the tickets the last one completes
   int32_t nstages;     // stages this workgroup contracts
   int32_t st_base;     // first of them
   int32_t st_total;    // stages of a whole row
   int32_t ks;          // splits of the stage range (split mode); 1 otherwise
-  float* partial;      // split mode: partial logits, [tile][split][register][thread]
+  float* partial;      // split mode: partial logits, [tile][split][expert / 4][token][expert mod 4]
   int32_t plan_cpl;    // 0: no plan; 1 or 2: the one-wave planner's candidates per lane
   PlanDeviceLaunch plan;   // the swap plan of the counts, made by the last workgroup
 };
@@ -473,11 +474,40 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
 }
 
+// Score of one logit without its bias lb (LBIAS: add it; padding experts hold -inf there and in sb).
+template <bool SIG, bool LBIAS>
+__device__ __forceinline__ float score_of(float logit, float lb, float sb) {
+  const float z = LBIAS ? logit + lb : logit;
+  if constexpr (SIG) return __builtin_amdgcn_rcpf(1.0f + __expf(-z)) + sb;
+  return z + 0.0f;                               // -0 -> +0; padding experts stay -inf
+}
+
+// Tokens [slice_begin(i), slice_begin(i + 1)) of a tile are finished by its split i.
+__device__ __forceinline__ int slice_begin(int i, int BM, int ks) { return i * BM / ks; }
+
+// Device-scope 16-byte accesses of the partial logits (sc1: past this XCD's L2, so they meet at the
+// point every XCD sees).  rsrc: raw buffer descriptor of the tile's partials.
+constexpr int kDeviceScope = 16;
+__device__ __forceinline__ void partial_store(const __amdgpu_buffer_rsrc_t& rsrc, const f32x4& v,
+                                              uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, off, 0, kDeviceScope);
+}
+__device__ __forceinline__ f32x4 partial_load(const __amdgpu_buffer_rsrc_t& rsrc, uint32_t off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, kDeviceScope));
+}
+
+// Polls of a tile's arrival word before a workgroup gives its slice to the tile's last arrival: each
+// takes about 0.7 us, so some 50 us, several times the spread of one launch's workgroups.
+constexpr int kArrivalPolls = 64;
+// Arrival word of a tile: arrivals in the low half, given-up slices (one bit per split) in the high.
+constexpr uint32_t kArrivalMask = 0xFFFFu;
+static_assert(kMaxSplits <= 16, "one given-up bit per split in the arrival word");
+
 // BM_: tokens per workgroup (the configuration's own, or half of it when that fills the chip better)
-// MODE: kFused contracts the whole row and finishes the tile; kSplit (split mode, grid tiles x ks)
-// contracts one of ks stage ranges and stores its partial logits, and the tile's last split to
-// arrive sums the tile's partials in split order and finishes the tile.
-constexpr int kFused = 0, kSplit = 1;
+// MODE: kFused contracts the whole row and finishes the tile.  Split mode (grid tiles x ks) contracts
+// one of ks stage ranges and exchanges partial logits through memory: in kSplit the tile's last split
+// to arrive adds them and finishes the tile, in kShare every split finishes its 1/ks of the tokens.
+constexpr int kFused = 0, kSplit = 1, kShare = 2;
 template <bool BF16, int EPAD, int BM_, int MODE>
 __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   using Cfg = TileCfg<EPAD>;
@@ -489,6 +519,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   constexpr int SROW = EPAD + 4;                 // score-tile row stride in floats
   constexpr int SCORE_BYTES = BM * SROW * 4;
   constexpr int SMEM = (NS * STAGE > SCORE_BYTES) ? NS * STAGE : SCORE_BYTES;
+  constexpr bool SHARE = MODE == kShare;
   constexpr int LPT = EPAD / 32;                 // lanes per token in the selection phase
   constexpr int TPP = kThreads / LPT;            // token slots (lane groups) of the workgroup
   // tokens a lane group works on at once: 1 (interleaving two ran slower on MI355X)
@@ -511,6 +542,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   __shared__ __attribute__((aligned(16))) float grp[BM][8];   // group scores (8 groups of 32)
   __shared__ __attribute__((aligned(16))) float gsc[GSC_TOK][kMaxGroups];
   __shared__ int32_t s_flag;
+  __shared__ uint32_t s_marks;
   __shared__ int64_t s_red[kWaves][2];
 
   const int tid = threadIdx.x;
@@ -520,10 +552,11 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int we = wave % WE;
   const int wt = wave / WE;
-  const int tile = MODE == kSplit ? (int)(blockIdx.x / (uint32_t)p.ks) : (int)blockIdx.x;
+  const int tile = MODE != kFused ? (int)(blockIdx.x / (uint32_t)p.ks) : (int)blockIdx.x;
+  const int split = MODE != kFused ? (int)(blockIdx.x % (uint32_t)p.ks) : 0;
+  const int chunk = MODE != kFused ? (p.st_total + p.ks - 1) / p.ks : p.st_total;   // stages per split
   const int64_t row0 = (int64_t)tile * BM;
   const int E = p.E;
-  constexpr int NACC = FE * FT * 16;               // accumulator registers per thread
 
   for (int i = tid; i < EPAD; i += kThreads) {
     hist[i] = 0;
@@ -542,68 +575,147 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
 
   {
     Params q = p;
-    if constexpr (MODE == kSplit) {
-      const int ks = (int)(blockIdx.x % (uint32_t)p.ks);
-      const int chunk = (p.st_total + p.ks - 1) / p.ks;
-      q.st_base = ks * chunk;
+    if constexpr (MODE != kFused) {
+      q.st_base = split * chunk;
       q.nstages = p.st_total - q.st_base < chunk ? p.st_total - q.st_base : chunk;
     }
     if (row0 < p.T && q.nstages > 0)
       contract<BF16, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem);
-    if constexpr (MODE == kSplit) {
-      // The partial goes out with device-scope stores, which are visible to every XCD once
-      // performed; each thread waits for its own, and the barrier orders them all before the
-      // arrival count.  The last split to arrive reads the partials back with device-scope loads
-      // (so not from a stale line of its own L2) and adds them in split order.  The loads of one
-      // 16-register block go out before any of them is used, so that a tile with many registers
-      // keeps them in flight together instead of waiting for each.
-      float* dst = p.partial + ((size_t)blockIdx.x * NACC) * kThreads + tid;
-#pragma unroll
-      for (int a = 0; a < FE; ++a)
-#pragma unroll
-        for (int b = 0; b < FT; ++b)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            __hip_atomic_store(&dst[(size_t)((a * FT + b) * 16 + r) * kThreads], acc[a][b][r],
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-      __syncthreads();
-      if (tid == 0) s_flag = atomicAdd(&p.ws_tile[tile], 1u) == (uint32_t)(p.ks - 1) ? 1 : 0;
-      __syncthreads();
-      if (s_flag != 1) return;
-      if (tid == 0) atomicExch(&p.ws_tile[tile], 0u);   // left zeroed for the next call
-      const float* src = p.partial + (size_t)tile * p.ks * NACC * kThreads + tid;
-#pragma unroll
-      for (int a = 0; a < FE; ++a)
-#pragma unroll
-        for (int b = 0; b < FT; ++b)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-      for (int ks = 0; ks < p.ks; ++ks) {
-#pragma unroll
-        for (int a = 0; a < FE; ++a)
-#pragma unroll
-          for (int b = 0; b < FT; ++b) {
-            f32x16 t;
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              t[r] = __hip_atomic_load(&src[((size_t)ks * NACC + (a * FT + b) * 16 + r) * kThreads],
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] += t[r];
-          }
-      }
-    }
   }
   lds_barrier();
+
+  float* S = reinterpret_cast<float*>(smem);
+  // ---- split mode: exchange the partial logits ------------------------------------------------
+  // Partials go to memory with device-scope stores; each thread waits for its own, and the barrier
+  // orders them all before the arrival count.  Sums are taken in split order, so results repeat.
+  __amdgpu_buffer_rsrc_t pr;
+  constexpr int kBlockBytes = BM * EPAD * 4;       // partials of one split
+  const int live = (p.st_total + chunk - 1) / chunk;   // splits that hold stages
+  uint32_t taken = 1;                              // slices this workgroup finishes, one bit each
+  if constexpr (MODE != kFused)
+    pr = __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<char*>(p.partial) +
+                                                   (size_t)tile * p.ks * kBlockBytes),
+                                           (short)0, p.ks * kBlockBytes, kRsrcWord3);
+  if constexpr (MODE == kSplit) {
+    // The tile's last split to arrive adds the partials and finishes the whole tile.  16 bytes are four experts of one token, at unit
+    // ((fe FT + ft) 4 + g) kThreads + thread; expert blocks past E are skipped.
+    auto unit_off = [&](int j, int fe, int ft, int g) {
+      return (uint32_t)(j * kBlockBytes + (((fe * FT + ft) * 4 + g) * kThreads + tid) * 16);
+    };
+    if (split < live) {
+#pragma unroll
+      for (int fe = 0; fe < FE; ++fe)
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            if (we * EW + fe * 32 + g * 8 < E)
+              partial_store(pr, f32x4{acc[fe][ft][g * 4], acc[fe][ft][g * 4 + 1], acc[fe][ft][g * 4 + 2],
+                                      acc[fe][ft][g * 4 + 3]}, unit_off(split, fe, ft, g));
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+    __syncthreads();
+    if (tid == 0) s_flag = atomicAdd(&p.ws_tile[tile], 1u) == (uint32_t)p.ks - 1 ? 1 : 0;
+    __syncthreads();
+    if (s_flag != 1) return;
+    taken = (1u << p.ks) - 1u;
+    constexpr int kJ = 4;                          // splits whose loads are in flight together
+#pragma unroll
+    for (int fe = 0; fe < FE; ++fe)
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[fe][ft][r] = 0.f;
+        for (int j0 = 0; j0 < live; j0 += kJ) {
+          f32x4 v[kJ][4];
+#pragma unroll
+          for (int j = 0; j < kJ; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+              v[j][g] = j0 + j < live && we * EW + fe * 32 + g * 8 < E
+                            ? partial_load(pr, unit_off(j0 + j, fe, ft, g)) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int j = 0; j < kJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[fe][ft][r] += v[j][r >> 2][r & 3];
+        }
+      }
+  }
+  if constexpr (SHARE) {
+    // Every split finishes its own slice of the tile's tokens.  Its partials of that slice go to the
+    // score tile in LDS, the others to memory (16 bytes, four experts of one token, at unit
+    // (expert / 4) BM + token of its block).  Once every split of the tile has arrived, the slice's
+    // partials are added and scored.
+    // A workgroup that waits too long for the others (they may still be queued behind another
+    // kernel's workgroups) stores its slice as well, marks it as given up and leaves; the tile's last
+    // arrival reads the marks with its own count and finishes those slices too.  So no workgroup
+    // depends on another one being resident, and the wait always ends.
+    const int s0 = slice_begin(split, BM, p.ks), s1 = slice_begin(split + 1, BM, p.ks);
+    const uint32_t pbase = (uint32_t)split * kBlockBytes;
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft) {
+      const int tl = wt * TW + ft * 32 + (lane & 31);
+      const bool own = tl >= s0 && tl < s1;
+#pragma unroll
+      for (int fe = 0; fe < FE; ++fe)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int e0 = we * EW + fe * 32 + g * 8 + (lane >> 5) * 4;
+          const f32x4 v = {acc[fe][ft][g * 4], acc[fe][ft][g * 4 + 1], acc[fe][ft][g * 4 + 2],
+                           acc[fe][ft][g * 4 + 3]};
+          if (own) *reinterpret_cast<f32x4*>(S + (tl - s0) * SROW + e0) = v;
+          else if (split < live && e0 < E)
+            partial_store(pr, v, pbase + (uint32_t)((e0 / 4) * BM + tl) * 16u);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+    __syncthreads();
+    if (tid == 0) {
+      const uint32_t old = atomicAdd(&p.ws_tile[tile], 1u);
+      int state = 0;                               // 1: every split has arrived
+      uint32_t marks = 0;
+      if ((old & kArrivalMask) == (uint32_t)p.ks - 1) {
+        state = 1;
+        marks = old >> 16;
+      }
+      for (int i = 0; state == 0 && i < kArrivalPolls; ++i) {
+        const uint32_t v = __hip_atomic_load(&p.ws_tile[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        state = (v & kArrivalMask) == (uint32_t)p.ks ? 1 : 0;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      s_flag = state;
+      s_marks = marks;
+    }
+    __syncthreads();
+    if (s_flag == 0) {
+      // give the slice up, unless the last split arrived in the meantime
+      if (split < live)
+        for (int i = tid; i < (s1 - s0) * (EPAD / 4); i += kThreads) {
+          const int t = i / (EPAD / 4), c = i % (EPAD / 4);
+          if (c * 4 < E)
+            partial_store(pr, *reinterpret_cast<const f32x4*>(S + t * SROW + c * 4),
+                          pbase + (uint32_t)(c * BM + s0 + t) * 16u);
+        }
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+      __syncthreads();
+      if (tid == 0)
+        s_flag = (atomicOr(&p.ws_tile[tile], 0x10000u << split) & kArrivalMask) == (uint32_t)p.ks ? 1 : 0;
+      __syncthreads();
+      if (s_flag == 0) return;
+    }
+    taken = s_marks | 1u << split;
+  }
+  const int tickets = MODE != kFused ? __builtin_popcount(taken) : 1;   // slices finished here
+  const int nslices = SHARE ? tickets : 1;         // a tile's one finisher takes it as a whole
 
   // Group-limited routing where the kept groups fill exactly half of a token's lanes (as with 8
   // groups of 32 keeping 4) finishes in a second selection phase on half the lanes (compact).
   // With exactly 8 groups of 32 the group scores come straight from the score computation
   // (early): each 32-expert block of a wave is one group, split over lanes l and l + 32.
+  // (A split's slice is a pass or two of the first phase, so it skips the second.)
   const int ng = p.n_group;
   const int gsz = E / ng;
-  const bool compact = NPASS % 2 == 0 && BM % TPASS == 0 && LPT >= 2 && ng > 1 && gsz >= 32 &&
+  const bool compact = !SHARE && NPASS % 2 == 0 && BM % TPASS == 0 && LPT >= 2 && ng > 1 && gsz >= 32 &&
                        p.topk_group * (gsz >> 5) * 2 == LPT;
   const bool early = compact && LPT == 8 && gsz == 32 && ng == 8 && p.kind == FB_SIGMOID &&
                      p.logit_bias == nullptr;
@@ -611,8 +723,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   // ---- logits and scores into an LDS tile S[token][expert] ------------------------
   // Lane l of a 32 x 32 block holds token (l & 31) and experts g * 8 + (l >> 5) * 4 + r in
   // register g * 4 + r.
-  float* S = reinterpret_cast<float*>(smem);
-  if (row0 < p.T) {
+  if (!SHARE && row0 < p.T) {
     if (p.logits) {                              // debug output of the early logits
 #pragma unroll
       for (int fe = 0; fe < FE; ++fe)
@@ -656,11 +767,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
             f32x4 sv;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const float z = LBIAS ? acc[fe][ft][g * 4 + r] + lb[r] : acc[fe][ft][g * 4 + r];
-              if constexpr (SIG)
-                sv[r] = __builtin_amdgcn_rcpf(1.0f + __expf(-z)) + sb[r];
-              else
-                sv[r] = z + 0.0f;                // -0 -> +0; padding experts stay -inf
+              sv[r] = score_of<SIG, LBIAS>(acc[fe][ft][g * 4 + r], lb[r], sb[r]);
               if constexpr (GROUPS) {
                 t2[fe][ft] = __builtin_amdgcn_fmed3f(t1[fe][ft], t2[fe][ft], sv[r]);
                 t1[fe][ft] = fmaxf(t1[fe][ft], sv[r]);
@@ -826,6 +933,87 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
       for (int r = 0; r < k; ++r) p.topk_idx[ttu * k + r] = list[r];
     }
   };
+  // split mode: the sum of the partials of tokens [t0, t0 + nt) and their scores, into rows 0 .. nt - 1
+  // of the score tile.  own: the split whose partials those rows already hold, -1 for none.
+  auto sum_slice = [&](auto sig_c, auto lbias_c, auto units_c, int t0, int nt, int own) {
+    constexpr bool SIG = decltype(sig_c)::value, LBIAS = decltype(lbias_c)::value;
+    constexpr int kU = decltype(units_c)::value;   // units per thread and splits per batch of loads
+    constexpr int kJ = 16 / kU;
+    const int units = nt * (EPAD / 4);
+    const float inv_nt = 1.0f / (float)nt;
+    for (int i0 = tid; i0 < units; i0 += kU * kThreads) {
+      f32x4 sum[kU];
+      int t[kU], c[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int i = i0 + u * kThreads;
+        c[u] = (int)(((float)i + 0.5f) * inv_nt);  // i / nt: i < 2^14, so the product is exact enough
+        t[u] = i - c[u] * nt;
+        sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      for (int j0 = 0; j0 < live; j0 += kJ) {
+        f32x4 v[kU][kJ];
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+#pragma unroll
+          for (int j = 0; j < kJ; ++j)
+            v[u][j] = partial_load(pr, i0 + u * kThreads < units && c[u] * 4 < E && j0 + j < live && j0 + j != own
+                                           ? (uint32_t)((j0 + j) * kBlockBytes) + (uint32_t)(c[u] * BM + t0 + t[u]) * 16u
+                                           : kOobOffset);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          f32x4 mine = {0.f, 0.f, 0.f, 0.f};
+          if (own >= j0 && own < j0 + kJ && i0 + u * kThreads < units)
+            mine = *reinterpret_cast<const f32x4*>(S + t[u] * SROW + c[u] * 4);
+#pragma unroll
+          for (int j = 0; j < kJ; ++j) sum[u] += j0 + j == own ? mine : v[u][j];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        if (i0 + u * kThreads >= units) continue;
+        const int e0 = c[u] * 4;
+        const f32x4 lb = *reinterpret_cast<const f32x4*>(s_lbias + e0);
+        const f32x4 sb = *reinterpret_cast<const f32x4*>(s_sbias + e0);
+        const int64_t tt = row0 + t0 + t[u];
+        if (p.logits && tt < p.T) {                // debug output of the early logits
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (e0 + r < E) p.logits[tt * E + e0 + r] = sum[u][r] + lb[r];
+        }
+        f32x4 sv;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sv[r] = score_of<SIG, LBIAS>(sum[u][r], lb[r], sb[r]);
+        *reinterpret_cast<f32x4*>(S + t[u] * SROW + e0) = sv;
+      }
+    }
+  };
+  for (int si = 0; si < nslices; ++si) {
+  int t0 = 0, nt = BM;                             // tokens of the tile in rows 0 .. nt - 1 of S
+  if constexpr (SHARE) {
+    const int own = si == 0 ? split : -1;
+    const int sl = si == 0 ? split : __builtin_ctz(taken);
+    taken &= ~(1u << sl);
+    t0 = slice_begin(sl, BM, p.ks);
+    nt = slice_begin(sl + 1, BM, p.ks) - t0;
+    using T1 = std::integral_constant<bool, true>;
+    using F0 = std::integral_constant<bool, false>;
+    // a slice that gives every thread one unit has up to 16 splits: all of them in one batch of loads
+    using U4 = std::integral_constant<int, 4>;
+    using U1 = std::integral_constant<int, 1>;
+    auto sum_by = [&](auto sig_c, auto lbias_c) {
+      if (nt * (EPAD / 4) <= kThreads) sum_slice(sig_c, lbias_c, U1{}, t0, nt, own);
+      else sum_slice(sig_c, lbias_c, U4{}, t0, nt, own);
+    };
+    if (p.kind == FB_SIGMOID) {
+      if (p.logit_bias) sum_by(T1{}, T1{});
+      else sum_by(T1{}, F0{});
+    } else {
+      sum_by(F0{}, T1{});
+    }
+    lds_barrier();
+  }
+  const int npass = SHARE ? (nt + TPASS - 1) / TPASS : NPASS;
   // each pass's scores are read while the previous pass is processed
   float snext[NT][32];
   if (!early) {
@@ -833,8 +1021,8 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   for (int u = 0; u < NT; ++u)
     if (u * TPP + gslot < BM) read_scores(snext[u], u * TPP + gslot);
 #pragma unroll 1
-  for (int pass = 0; pass < NPASS; ++pass) {
-    if (pass * TPASS + gslot >= BM) continue;  // whole waves (checked above)
+  for (int pass = 0; pass < npass; ++pass) {
+    if (pass * TPASS + (gslot & ~(64 / LPT - 1)) >= nt) continue;  // whole waves
     int tl[NT];
     int64_t tt[NT];
     bool tvalid[NT];
@@ -842,8 +1030,8 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
       tl[u] = pass * TPASS + u * TPP + gslot;
-      tt[u] = row0 + tl[u];
-      tvalid[u] = tt[u] < p.T;
+      tt[u] = row0 + t0 + tl[u];
+      tvalid[u] = tt[u] < p.T && (!SHARE || tl[u] < nt);
 #pragma unroll
       for (int i = 0; i < 32; ++i) s[u][i] = snext[u][i];
       if (tl[u] + TPASS < BM) read_scores(snext[u], tl[u] + TPASS);
@@ -1012,6 +1200,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
     }
   }
   lds_barrier();
+  }
 
   // ---- one global atomic per expert per workgroup, then the completion ticket ----------------
   // Workgroups exchange data only through device-scope atomics, which are coherent across the
@@ -1027,7 +1216,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   }
   if (done < 0) s_flag = -1;                   // never true (counters stay below 2^31); uses the values
   __syncthreads();
-  if (tid == 0) s_flag = (atomicAdd(p.ws_ticket, 1u) == p.nblocks - 1) ? 1 : 0;
+  if (tid == 0) s_flag = (atomicAdd(p.ws_ticket, (uint32_t)tickets) == p.nblocks - (uint32_t)tickets) ? 1 : 0;
   __syncthreads();
   if (s_flag != 1) return;
 
@@ -1035,6 +1224,9 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   int32_t* rl = reinterpret_cast<int32_t*>(smem);
   for (int r = tid; r < p.R; r += kThreads) rl[r] = 0;
   if (tid == 0) s_flag = 0;
+  // every workgroup is past its wait once the last ticket is taken: the arrival words go back to zero
+  if constexpr (MODE != kFused)
+    for (int i = tid; i < (int)(p.nblocks / (uint32_t)p.ks); i += kThreads) atomicExch(&p.ws_tile[i], 0u);
   __syncthreads();
   // the swap plan's tables are fetched while the counters are read, and go straight to the
   // planner's LDS (its arrays lie past the rank loads at the start of smem); R * S <= 704 and E <= 256
@@ -1109,17 +1301,34 @@ int epad_of(int32_t E) {
 }
 
 // Split mode: when the tiles would occupy at most half of the CUs, the stage range of every tile
-// is split over up to four workgroups (at least four stages each), so that more CUs stream the
-// hidden rows and each streams a share of the router weight.
-int split_count(int64_t T, int BM, int st_total, int num_cus) {
+// is split over several workgroups, so that more CUs stream the hidden rows and each streams a share
+// of the router weight.  `room`: bytes for the partials.
+//   * At least four stages per split (two where 16 splits are allowed): below that the first loads'
+//     latency is most of a split's time (E = 128, H = 2048, T = 1000: 19.8 us with 2 splits of 4
+//     stages, 23.0 us with 4 of 2).
+//   * Up to 8 splits, 16 for at most four 256-expert tiles.  E = 256, H = 7168, per pass with its
+//     plan, 4 / 8 / 16 splits: T = 64 39.1 / 33.5 / 31.7 us, T = 192 38.6 / 34.0 / 32.4, T = 500
+//     38.5 / 34.4 / 35.5, T = 1237 39.7 / 39.1 / 39.6.
+int split_count(int64_t T, int BM, int epad, int st_total, int num_cus, size_t room) {
   const int64_t tiles = (T + BM - 1) / BM;
-  // split mode: at most half of the CUs hold tiles, and each tile has an arrival counter
+  // split mode: at most half of the CUs hold tiles, and each tile has an arrival word
   if (T <= 0 || tiles * 2 > num_cus || tiles > kMaxSplitTiles) return 1;
+  const bool few = epad == 256 && tiles <= 4 && st_total >= 2 * kMaxSplits;
   int64_t ks = num_cus / tiles;
-  if (ks > 4) ks = 4;
-  if (ks > st_total / 4) ks = st_total / 4;
+  const int64_t most = few ? kMaxSplits : st_total / 4 < 8 ? st_total / 4 : 8;
+  if (ks > most) ks = most;
+  const size_t per_split = (size_t)tiles * BM * epad * sizeof(float);
+  if ((size_t)ks * per_split > room) ks = (int64_t)(room / per_split);
   return ks > 1 ? (int)ks : 1;
 }
+
+// Whether every split finishes a slice of its tile.  Worth it where the tile's selection and outputs
+// take longer than the exchange: 256 experts in at least four slices.  The last split finishing the
+// whole tile instead / slices (us per pass with its plan): E = 256, H = 7168, T = 4096 in 4 splits
+// 46.9 / 46.5 (float32 with selections and logits written 142 / 133), T = 6000 in 2 splits 55.8 /
+// 57.4; E = 128, H = 2048, T = 4000 in 2 splits 24.2 / 28.2; E = 64, T = 3000 19.1 / 23.6.
+constexpr bool can_share(int epad) { return epad == 256; }
+bool shares(int epad, int ks) { return can_share(epad) && ks >= 4; }
 
 // Tile height of a launch (see launch_cfg).
 template <int EPAD>
@@ -1136,7 +1345,7 @@ template <int EPAD>
 size_t split_bytes_cfg(int64_t T, int32_t H, int32_t dtype, int num_cus) {
   const int BM = tile_rows<EPAD>(T, num_cus);
   const int st_total = (H * (dtype == FB_BF16 ? 2 : 4) + kStageRowBytes - 1) / kStageRowBytes;
-  const int ks = split_count(T, BM, st_total, num_cus);
+  const int ks = split_count(T, BM, EPAD, st_total, num_cus, SIZE_MAX);
   if (ks <= 1) return 0;
   const int64_t tiles = (T + BM - 1) / BM;
   return (size_t)tiles * ks * BM * EPAD * sizeof(float);
@@ -1185,7 +1394,7 @@ int launch_cfg_bm(const PredictLaunch& a) {
   p.st_total = (p.Hbytes + kStageRowBytes - 1) / kStageRowBytes;
   p.nstages = p.st_total;
   p.st_base = 0;
-  p.ks = split_count(a.T, BM, p.st_total, a.num_cus);
+  p.ks = a.partial != nullptr ? split_count(a.T, BM, EPAD, p.st_total, a.num_cus, a.partial_bytes) : 1;
   p.partial = a.partial;
   p.plan_cpl = 0;
   if (a.plan != nullptr) {
@@ -1193,12 +1402,17 @@ int launch_cfg_bm(const PredictLaunch& a) {
     p.plan_cpl = (int64_t)a.plan->S * a.plan->S <= 64 ? 1 : 2;
   }
   hipStream_t st = static_cast<hipStream_t>(a.stream);
-  if (p.ks > 1 && a.partial != nullptr &&
-      a.partial_bytes >= (size_t)tiles * p.ks * BM * EPAD * sizeof(float)) {
-    hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kSplit>), dim3(p.nblocks * p.ks),
-                       dim3(kThreads), 0, st, p);
+  if (p.ks > 1) {
+    p.nblocks = (uint32_t)(tiles * p.ks);
+    if constexpr (can_share(EPAD)) {
+      if (shares(EPAD, p.ks))
+        hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kShare>), dim3(p.nblocks), dim3(kThreads),
+                           0, st, p);
+    }
+    if (!shares(EPAD, p.ks))
+      hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kSplit>), dim3(p.nblocks), dim3(kThreads),
+                         0, st, p);
   } else {
-    p.ks = 1;
     hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kFused>), dim3(p.nblocks), dim3(kThreads),
                        0, st, p);
   }

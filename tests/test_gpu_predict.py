@@ -428,6 +428,37 @@ def test_split_mode_parity(name, T):
     _say(f"[split] {name} T={T} ok {stats}")
 
 
+# E, T, H, dtype: one token; two and four tiles in 16 splits (33 stages: five of them empty);
+# five tiles in 8 splits of uneven stages; an expert count inside a 32-expert block; 21 tiles
+@pytest.mark.parametrize("E,T,H,dtype", [(256, 1, 4096, "bf16"), (256, 65, 2064, "f32"),
+                                         (256, 255, 4224, "bf16"), (256, 257, 4224, "bf16"),
+                                         (200, 130, 4096, "bf16"), (256, 1300, 4096, "bf16"),
+                                         (8, 70, 4128, "bf16"), (48, 129, 4096, "bf16")])
+def test_split_slices(E, T, H, dtype):
+    """Many splits of a tile, at the edges of tiles, slices and stage ranges: oracle parity, repeats
+    that are bit-identical, a clean workspace header, and the same checks with half the room for
+    partials, where a batch runs in fewer splits."""
+    wl = dataclasses.replace(CONFIGS["dsv3"].with_T(T), H=H, E=E, dtype=dtype, n_clusters=E, k=min(8, E // 2))
+    if E != 256:
+        wl = dataclasses.replace(wl, n_group=1, topk_group=1, group_topn=1)
+    e2r = np.arange(E, dtype=np.int32) % wl.R
+    need = fb.predict_split_workspace_bytes(T, E, H, torch.bfloat16 if dtype == "bf16" else torch.float32)
+    _say(f"[slices] E={E} T={T} H={H} {dtype} workspace {need}")
+    assert need > 2048
+    li = make_layer(wl, 2)
+    half = fb.Predictor(split=False)
+    half._reserve(2048 + (need - 2048) // 2, None)
+    for pred in (fb.Predictor(), half):
+        a = run_gpu(li, wl, e2r, predictor=pred, packed=True)
+        check_prediction(a, li, wl, e2r, label=f"slices E={E} T={T}")
+        check_counts_consistent(a, wl, e2r)
+        b = run_gpu(li, wl, e2r, predictor=pred, packed=True)
+        for key in ("counts", "rank_loads", "topk"):
+            assert np.array_equal(a[key], b[key]), key
+        assert np.array_equal(a["logits"].view(np.uint32), b["logits"].view(np.uint32))
+        assert not pred.workspace[:2048].cpu().numpy().any()
+
+
 def test_qwen3_layers_back_to_back():
     """Qwen3-MoE-shaped layers (every token against the oracle) and the device plan of each layer's
     counts under the config's budget against the oracle's plan.  All 48 layers run in bench.py's
