@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "fb_internal.h"
 
 namespace fb {
@@ -245,19 +247,57 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
   return readlane_u64(v, 0) + readlane_u64(v, 16) + readlane_u64(v, 32) + readlane_u64(v, 48);
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
-  return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
-             max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+// Wave reductions of the rounds below: each row of 16 lanes by DPP (lane ^ 1, lane ^ 2, the mirror
+// within 8 lanes, the mirror within 16), then row 0 into row 1 and row 2 into row 3 (row_bcast 15)
+// and rows 0-1 into rows 2-3 (row_bcast 31), so that lane 63 ends with the whole wave's.  The sets
+// merged at each step are disjoint.  `id` is what a lane that receives nothing gets.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_rows(uint32_t v, uint32_t id) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)id, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <class STEP>
+__device__ __forceinline__ void wave_steps(const STEP& step) {
+  using std::integral_constant;
+  step(integral_constant<int, 0xB1>{}, integral_constant<int, 0xF>{});    // quad_perm [1,0,3,2]
+  step(integral_constant<int, 0x4E>{}, integral_constant<int, 0xF>{});    // quad_perm [2,3,0,1]
+  step(integral_constant<int, 0x141>{}, integral_constant<int, 0xF>{});   // row_half_mirror
+  step(integral_constant<int, 0x140>{}, integral_constant<int, 0xF>{});   // row_mirror
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});   // row_bcast 15 into rows 1, 3
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});   // row_bcast 31 into rows 2, 3
+}
+__device__ __forceinline__ uint32_t wave_min_uniform(uint32_t v) {
+  wave_steps([&](auto ctrl, auto rows) {
+    v = min(v, dpp_rows<decltype(ctrl)::value, decltype(rows)::value>(v, ~0u));
+  });
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// Largest and second largest of v (the largest again when two lanes hold it).
+__device__ __forceinline__ void wave_top2_uniform(uint32_t v, uint32_t& largest, uint32_t& second) {
+  uint32_t m1 = v, m2 = 0;
+  wave_steps([&](auto ctrl, auto rows) {
+    constexpr int C = decltype(ctrl)::value, W = decltype(rows)::value;
+    const uint32_t o1 = dpp_rows<C, W>(m1, 0u), o2 = dpp_rows<C, W>(m2, 0u);
+    m2 = max(min(m1, o1), max(m2, o2));
+    m1 = max(m1, o1);
+  });
+  largest = (uint32_t)__builtin_amdgcn_readlane((int)m1, 63);
+  second = (uint32_t)__builtin_amdgcn_readlane((int)m2, 63);
 }
 
-// Rounds of the one-wave planner when every rank sits in its own lane (R <= 64), every load fits
-// 31 bits and there are no replicas (item ids below E + R * S <= 8192): loads, extremes and tie keys
-// are 32-bit, rank ties are resolved by the lowest lane of a
-// ballot, and the tie key reduction runs only when two candidates share the best benefit.
+// Rounds of the one-wave planner when every rank sits in its own lane (R <= 64), the loads sum to
+// less than 2^30 and there are no replicas (item ids below E + R * S <= 8192).
+// Between the two frontier ranks, with D = M - L_min > 0, a candidate with load difference
+// d = l_j - l_i leaves them at their mean +- (D + 2d) / 2, so with u = |D + 2d| its benefit is
+//     den (M - max(o, (M + L_min + u) / 2)) + num (D^2 - u^2) / 2
+// (o the largest load outside the pair), which falls strictly as u grows: the round's best is the
+// smallest u, then the smallest item ids, and its benefit is positive exactly when u < D.  With
+// num = 0 the benefit stops falling once (M + L_min + u) / 2 is below o, so u counts as no less than
+// 2 o - M - L_min there.  u <= M + L_min < 2^30.
+// A round is a serial chain in one wave with nothing to hide it, so it costs its instructions (about
+// four cycles each) plus one LDS round trip: the benefits and the swap records are formed once at
+// the end, one lane per swap, from what each round leaves in that lane.  Reducing 64-bit benefits in
+// two halves, with a third reduction for o and the record built in every round, took 0.73 us a round
+// (E = 256 on 32 ranks); this takes 0.46 us.
 // Returns the number of swaps written.
 // CPL: candidates per lane (1 when S * S <= 64, else 2).
 template <int CPL>
@@ -267,7 +307,7 @@ __device__ __forceinline__ int rounds_small(const PlanDeviceLaunch& a, uint2* sl
   const int E = a.E, R = a.R, S = a.S;
   const fb_budget bg = a.budget;
   const bool valid = lane < R;
-  // candidates (p, q) = (c / S, c mod S) for c = lane (+ 64)
+  // candidates (p, q) = (c / S, c mod S) for c = lane (+ 64); the others read slot 0 and never count
   int pc[CPL], qc[CPL];
   bool hc[CPL];
 #pragma unroll
@@ -278,90 +318,95 @@ __device__ __forceinline__ int rounds_small(const PlanDeviceLaunch& a, uint2* sl
     qc[h] = hc[h] ? c - pc[h] * S : 0;
   }
   const bool capped = bg.per_rank_cap != 0;
+  const bool flat_top = g_num == 0 && R > 2;
+  const int32_t tau = bg.tau < INT32_MAX ? (int32_t)bg.tau : INT32_MAX;
   constexpr uint32_t kMoved = 0x80000000u;
+  uint32_t lo = valid ? Lu : ~0u;              // this rank's load for the minimum
+  if (!valid) Lu = 0;                          // ... and for the maximum
+  // what swap s leaves in lane s mod 64
+  uint32_t r_place = 0, r_items = 0, r_M = 0, r_min = 0, r_other = 0;
+  int32_t r_d = 0;
+  auto flush = [&](int from, int n) {          // swaps from .. from + n - 1, one per lane
+    if (lane >= n) return;
+    const int64_t M = r_M, Lmin = r_min, d = r_d;
+    int64_t m2 = M + d > Lmin - d ? M + d : Lmin - d;
+    if (R > 2 && (int64_t)r_other > m2) m2 = r_other;
+    const uint32_t wi = r_items & 0xFFFFu, wj = r_items >> 16;
+    fb_swap sw;
+    sw.src_rank = (int32_t)(r_place & 255u);
+    sw.dst_rank = (int32_t)((r_place >> 8) & 255u);
+    sw.src_slot = (int32_t)((r_place >> 16) & 255u);
+    sw.dst_slot = (int32_t)(r_place >> 24);
+    sw.expert_src = wi < (uint32_t)E ? (int32_t)wi : -1;
+    sw.expert_dst = wj < (uint32_t)E ? (int32_t)wj : -1;
+    sw.gain = g_den * (M - m2) + g_num * (2 * d * (Lmin - M - d));
+    a.swaps[from + lane] = sw;
+  };
   int ns = 0;
-  for (int round = 0; round < bg.max_swaps; ++round) {
-    const uint32_t M32 = wave_max_u32(valid ? Lu : 0u);
-    const uint32_t Lmin32 = ~wave_max_u32(valid ? ~Lu : 0u);
-    const int amax = (int)__builtin_ctzll(__ballot(valid && Lu == M32));
-    const int amin = (int)__builtin_ctzll(__ballot(valid && Lu == Lmin32));
-    const int64_t M = M32, Lmin = Lmin32;
-    if (M - Lmin <= bg.tau) break;
-    const uint32_t ko = wave_max_u32(valid && lane != amax && lane != amin ? Lu + 1u : 0u);
-    const int64_t other = ko ? (int64_t)ko - 1 : INT64_MIN;
+  for (; ns < bg.max_swaps; ++ns) {
+    // the largest load outside the pair is the second largest of all: with three ranks or more one
+    // of them is at least as loaded as the least loaded rank
+    uint32_t M, second;
+    wave_top2_uniform(Lu, M, second);
+    const uint32_t Lmin = wave_min_uniform(lo);
+    const int32_t D = (int32_t)(M - Lmin);
+    if (D <= tau) break;
+    const int amax = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(Lu == M));   // M > 0 here
+    const int amin = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(lo == Lmin));
+    if (capped && (part[amax] >= bg.per_rank_cap || part[amin] >= bg.per_rank_cap)) break;
+    const int32_t flat = flat_top ? 2 * (int32_t)second - (int32_t)(M + Lmin) : 0;
 
-    // this lane's better candidate: larger benefit, then smaller (i, j)
-    bool ok = false;
-    int64_t gain = 0;
-    uint32_t tk = 0;
+    // this lane's better candidate: smaller u, then smaller (i, j); ~0u when it has none
+    uint32_t bu = ~0u, tk = 0;
     uint2 ea = {0u, 0u}, eb = {0u, 0u};
-    int pl = 0, ql = 0;
-    const bool cap_hit = capped && (part[amax] >= bg.per_rank_cap || part[amin] >= bg.per_rank_cap);
-    auto eval = [&](int p, int q, uint2& xa, uint2& xb, int64_t& gh, uint32_t& th) -> bool {
-      xa = slot[amax * S + p];
-      xb = slot[amin * S + q];
-      const uint32_t i = xa.x & ~kMoved, j = xb.x & ~kMoved;
-      const int64_t d = (int64_t)(int32_t)xb.y - (int64_t)(int32_t)xa.y;
-      const int64_t la = M + d, lb = Lmin - d;
-      int64_t m2 = la > lb ? la : lb;
-      if (other > m2) m2 = other;
-      const int64_t spread = g_num ? g_num * (2 * d * (Lmin - M - d)) : 0;
-      gh = g_den * (M - m2) + spread;
-      th = (i << kSmallItemBits) | j;
-      return !cap_hit && !((xa.x | xb.x) & kMoved) && !(i >= (uint32_t)E && j >= (uint32_t)E) && gh > 0;
-    };
-    if constexpr (CPL == 1) {
-      if (hc[0]) {
-        ok = eval(pc[0], qc[0], ea, eb, gain, tk);
-        pl = pc[0];
-        ql = qc[0];
-      }
-    } else {
+    int bh = 0;
 #pragma unroll
-      for (int h = 0; h < CPL; ++h) {
-        if (!hc[h]) continue;
-        uint2 xa, xb;
-        int64_t gh;
-        uint32_t th;
-        const bool okh = eval(pc[h], qc[h], xa, xb, gh, th);
-        if (okh && (!ok || gh > gain || (gh == gain && th < tk))) {
-          ok = true; gain = gh; tk = th; ea = xa; eb = xb; pl = pc[h]; ql = qc[h];
-        }
-      }
+    for (int h = 0; h < CPL; ++h) {
+      const uint2 xa = slot[amax * S + pc[h]], xb = slot[amin * S + qc[h]];
+      const uint32_t i = xa.x & ~kMoved, j = xb.x & ~kMoved;
+      const int32_t x = D + 2 * ((int32_t)xb.y - (int32_t)xa.y);
+      const uint32_t th = (i << kSmallItemBits) | j;
+      const bool ok = hc[h] & ((int32_t)(xa.x | xb.x) >= 0) & (min(i, j) < (uint32_t)E);
+      const uint32_t u = ok ? (uint32_t)max(x < 0 ? -x : x, flat) : ~0u;
+      const bool take = h == 0 || u < bu || (u == bu && th < tk);
+      bu = take ? u : bu;
+      tk = take ? th : tk;
+      ea.x = take ? xa.x : ea.x; ea.y = take ? xa.y : ea.y;
+      eb.x = take ? xb.x : eb.x; eb.y = take ? xb.y : eb.y;
+      bh = take ? h : bh;
     }
-    // largest benefit as two 32-bit reductions, then the smallest (i, j) among equal benefits
-    const uint32_t ghi = wave_max_u32(ok ? (uint32_t)((uint64_t)gain >> 32) : 0u);
-    const uint32_t glo = wave_max_u32(ok && (uint32_t)((uint64_t)gain >> 32) == ghi ? (uint32_t)gain : 0u);
-    const uint64_t g = ((uint64_t)ghi << 32) | glo;
-    if (g == 0) break;                          // no admissible candidate with positive benefit
-    const bool best = ok && (uint64_t)gain == g;
-    uint64_t win = __ballot(best);
-    if (__builtin_popcountll(win) > 1) {
-      const uint32_t tmin = ~wave_max_u32(best ? ~tk : 0u);
-      win = __ballot(best && tk == tmin);
+    const uint32_t u = wave_min_uniform(bu);
+    if (u >= (uint32_t)D) break;                // no candidate with positive benefit
+    uint64_t win = __builtin_amdgcn_ballot_w64(bu == u);
+    if ((win & (win - 1)) != 0) {
+      const uint32_t tmin = wave_min_uniform(bu == u ? tk : ~0u);
+      win = __builtin_amdgcn_ballot_w64(bu == u && tk == tmin);
     }
     const int wl = (int)__builtin_ctzll(win);
-    const int wp = __builtin_amdgcn_readlane(pl, wl), wq = __builtin_amdgcn_readlane(ql, wl);
-    const uint32_t wi = (uint32_t)__builtin_amdgcn_readlane((int)(ea.x & ~kMoved), wl);
-    const uint32_t wj = (uint32_t)__builtin_amdgcn_readlane((int)(eb.x & ~kMoved), wl);
-    const int32_t ci = __builtin_amdgcn_readlane((int)ea.y, wl), cj = __builtin_amdgcn_readlane((int)eb.y, wl);
-    const int32_t d = cj - ci;
-    if (lane == 0) {
-      slot[amax * S + wp] = make_uint2(wj | kMoved, (uint32_t)cj);
-      slot[amin * S + wq] = make_uint2(wi | kMoved, (uint32_t)ci);
-      ++part[amax];
-      ++part[amin];
-      fb_swap sw;
-      sw.src_rank = amax; sw.dst_rank = amin; sw.src_slot = wp; sw.dst_slot = wq;
-      sw.expert_src = wi < (uint32_t)E ? (int32_t)wi : -1;
-      sw.expert_dst = wj < (uint32_t)E ? (int32_t)wj : -1;
-      sw.gain = (int64_t)g;
-      a.swaps[ns] = sw;
+    const int p = CPL == 1 || bh == 0 ? pc[0] : pc[CPL - 1], q = CPL == 1 || bh == 0 ? qc[0] : qc[CPL - 1];
+    const int32_t d = __builtin_amdgcn_readlane((int)(eb.y - ea.y), wl);
+    const uint32_t items = (uint32_t)__builtin_amdgcn_readlane((int)(ea.x | eb.x << 16), wl);
+    const uint32_t slots = (uint32_t)__builtin_amdgcn_readlane(p | q << 8, wl);
+    if (lane == wl) {
+      slot[amax * S + p] = make_uint2(eb.x | kMoved, eb.y);
+      slot[amin * S + q] = make_uint2(ea.x | kMoved, ea.y);
+      if (capped) { ++part[amax]; ++part[amin]; }
     }
-    Lu += (uint32_t)((lane == amax ? d : 0) - (lane == amin ? d : 0));
-    ++ns;
+    const int at = ns & 63;
+    const bool mine = lane == at;
+    r_place = mine ? (uint32_t)(amax | amin << 8) | slots << 16 : r_place;
+    r_items = mine ? items : r_items;
+    r_M = mine ? M : r_M;
+    r_min = mine ? Lmin : r_min;
+    r_other = mine ? second : r_other;
+    r_d = mine ? d : r_d;
+    const int32_t delta = (lane == amax ? d : 0) - (lane == amin ? d : 0);
+    Lu += (uint32_t)delta;
+    lo += (uint32_t)delta;
+    if (at == 63) flush(ns - 63, 64);
     plan_sync<64>();
   }
+  flush(ns & ~63, ns & 63);
   return ns;
 }
 
@@ -385,12 +430,18 @@ struct PlanWaveLds {
   int64_t* ebytes;
   int64_t* acc_cost;
   int32_t* acc_pair;
+  // tables laid out by the caller (one rank per lane): state of its check and the rank loads
+  int32_t* state;
+  unsigned long long* load;
 };
+// Bits of *state: a value or size out of range; replicas (values >= E), whose tables only the full
+// check settles; some expert not in the table exactly once.
+constexpr int kPlanBad = 1, kPlanNotOnce = 2, kPlanReplicas = 4;
 
 // Bytes of PlanWaveLds for CAP slots and RPL ranks per lane, laid out as plan_wave_lds carves them.
 constexpr size_t plan_wave_lds_bytes(int CAP, int RPL) {
   return (size_t)CAP * 8 + (RPL == 1 ? (size_t)CAP * 8 + (size_t)kMaxTimedSwaps * 12 : 0) +
-         (size_t)CAP * 4 * 6 + (size_t)64 * RPL * 4 + 8;
+         (size_t)CAP * 4 * 6 + (size_t)64 * RPL * 4 + 16 + (RPL == 1 ? 64 * 8 : 0);
 }
 // Carves PlanWaveLds out of `mem` (8-byte aligned, plan_wave_lds_bytes(CAP, RPL) bytes).
 __device__ __forceinline__ PlanWaveLds plan_wave_lds(char* mem, int CAP, int RPL) {
@@ -400,7 +451,10 @@ __device__ __forceinline__ PlanWaveLds plan_wave_lds(char* mem, int CAP, int RPL
   l.ebytes = nullptr;
   l.acc_cost = nullptr;
   l.acc_pair = nullptr;
+  l.load = nullptr;
   if (RPL == 1) {
+    l.load = reinterpret_cast<unsigned long long*>(m);
+    m += 64 * 8;
     l.ebytes = reinterpret_cast<int64_t*>(m);
     m += (size_t)CAP * 8;
     l.acc_cost = reinterpret_cast<int64_t*>(m);
@@ -415,20 +469,22 @@ __device__ __forceinline__ PlanWaveLds plan_wave_lds(char* mem, int CAP, int RPL
   l.flag = w; w += CAP;
   if (RPL == 1) { l.acc_pair = w; w += kMaxTimedSwaps; }
   l.part = w; w += 64 * RPL;
-  l.bad = w; l.jmax = w + 1;
+  l.bad = w; l.jmax = w + 1; l.state = w + 2;
   return l;
 }
 
 // RPL: ranks per lane (R <= 64 * RPL); rank r lives in lane r % 64, register r / 64.
 // CPL: candidates per lane, 1 for S * S <= 64, 2 for S * S <= 128.
 // Runs in the first wave of its workgroup (threadIdx.x < 64); the caller's other waves take no part.
-// TABLES_IN_LDS: the caller has already put the counts in lds.cnt, the slot table in lds.vals and,
-// under a time budget, the expert sizes in lds.ebytes (all published by a barrier).
+// PREPARED: the caller has already put the counts in lds.cnt, the slot table in lds.vals, under a
+// time budget the expert sizes in lds.ebytes, zeros in lds.part and the state of its short check in
+// lds.state, and, for a table that passes it, the slot entries and the rank loads in lds.slot and
+// lds.load (all published by a barrier); node_in is the lane's rank_node under a time budget.
 // Time budgets (a.timed) need RPL 1: every candidate between the two frontier ranks is costed by
 // Eq. 9 on their link, admitted if it fits what is left of both ranks' and of the link's budgets,
 // and the round's best is the largest benefit / cost, then the tie key.
-template <int RPL, int CPL, bool TABLES_IN_LDS = false>
-__device__ void plan_wave_body(const PlanDeviceLaunch& a, const PlanWaveLds& lds) {
+template <int RPL, int CPL, bool PREPARED = false>
+__device__ void plan_wave_body(const PlanDeviceLaunch& a, const PlanWaveLds& lds, int32_t node_in = 0) {
   int32_t* const vals = lds.vals;      // the input tables
   int32_t* const cnt = lds.cnt;
   int32_t* const ej = lds.ej;
@@ -446,62 +502,73 @@ __device__ void plan_wave_body(const PlanDeviceLaunch& a, const PlanWaveLds& lds
   int64_t* const ebytes = lds.ebytes;
   const float inv_e = 1.0f / (float)E;
 
-  // every input table is fetched before the first wait
-  for (int e = lane; e < E; e += 64) {
-    if (!TABLES_IN_LDS) {
+  // time budget: rank `lane`'s node and what is left of its budget
+  int32_t node_r = node_in;
+  int64_t left_r = a.cost.rank_budget_ns;
+  int state = 0;
+  if constexpr (PREPARED) {
+    state = *lds.state;
+  } else {
+    // every input table is fetched before the first wait
+    for (int e = lane; e < E; e += 64) {
       cnt[e] = a.counts[e];
       if (timed) ebytes[e] = a.expert_bytes[e];
+      reps[e] = 0;
     }
-    reps[e] = 0;
-  }
-  if (!TABLES_IN_LDS)
     for (int c = lane; c < RS; c += 64) vals[c] = a.slot_expert[c];
-  for (int r = lane; r < R; r += 64) part[r] = 0;
-  // time budget: rank `lane`'s node and what is left of its budget
-  const int32_t node_r = timed && lane < R ? a.rank_node[lane] : 0;
-  int64_t left_r = a.cost.rank_budget_ns;
-  plan_sync<64>();
-  // short check of a plain placement (every expert exactly once); a replica (a value >= E) sends the
-  // table to the full check
-  int bad = 0, replica = 0;
-  for (int c = lane; c < RS; c += 64) {
-    const int v = vals[c];
-    if (v < -1) bad = 1;
-    else if (v >= E) replica = 1;
-    else if (v >= 0) atomicAdd(&reps[v], 1);
+    for (int r = lane; r < R; r += 64) part[r] = 0;
+    node_r = timed && lane < R ? a.rank_node[lane] : 0;
+    plan_sync<64>();
+    // short check of a plain placement (every expert exactly once)
+    for (int c = lane; c < RS; c += 64) {
+      const int v = vals[c];
+      if (v < -1) state |= kPlanBad;
+      else if (v >= E) state |= kPlanReplicas;
+      else if (v >= 0) atomicAdd(&reps[v], 1);
+    }
+    plan_sync<64>();
+    for (int e = lane; e < E; e += 64) {
+      if (reps[e] != 1) state |= kPlanNotOnce;
+      if (cnt[e] < 0 || (timed && (ebytes[e] < 0 || ebytes[e] > kCostLimit))) state |= kPlanBad;
+    }
   }
-  plan_sync<64>();
+  const bool replicas = __ballot(state & kPlanReplicas) != 0;
   int J = 1;
-  if (__ballot(replica)) {
+  bool any_bad;
+  if (replicas) {
+    // a value out of range is found again by the full check, a size out of range is not
     if (lane == 0) s_bad = 0;
     check_placement<64>(E, R, S, vals, cnt, ej, reps, base, flag, nullptr, &s_bad, &s_J);
     J = s_J;
-    bad = s_bad;
+    any_bad = s_bad != 0 || __ballot(state & kPlanBad) != 0;
   } else {
-    for (int e = lane; e < E; e += 64) bad |= (reps[e] != 1) | (cnt[e] < 0);
+    any_bad = __ballot(state & (kPlanBad | kPlanNotOnce)) != 0;
   }
-  if (timed)
-    for (int e = lane; e < E; e += 64) bad |= (ebytes[e] < 0) | (ebytes[e] > kCostLimit);
   const int V = E * J;               // slot values are below V; empty-slot ids from V
-  const bool any_bad = __ballot(bad) != 0;
   if (any_bad || (int64_t)V + RS > ((int64_t)1 << kItemBits)) {
     if (lane == 0) { *a.n_swaps = 0; *a.status = any_bad ? FB_EINVAL : FB_EUNSUPPORTED; }
     return;
   }
-  for (int c = lane; c < RS; c += 64) {
-    const int v = vals[c];
-    slot[c] = v < 0 ? make_uint2((uint32_t)(V + c), 0u)
-                    : make_uint2((uint32_t)v, (uint32_t)(J == 1 ? cnt[v] : replica_share(ej[c], cnt, reps)));
+  const bool laid_out = PREPARED && !replicas;
+  if (!laid_out) {
+    for (int c = lane; c < RS; c += 64) {
+      const int v = vals[c];
+      slot[c] = v < 0 ? make_uint2((uint32_t)(V + c), 0u)
+                      : make_uint2((uint32_t)v, (uint32_t)(J == 1 ? cnt[v] : replica_share(ej[c], cnt, reps)));
+    }
+    plan_sync<64>();
   }
-  plan_sync<64>();
   int64_t Lr[RPL];                   // load of rank lane + 64 m (0 past R)
   int64_t mine = 0;
 #pragma unroll
   for (int m = 0; m < RPL; ++m) {
     const int r = lane + 64 * m;
     int64_t v = 0;
-    if (r < R)
+    if (laid_out) {
+      v = r < R ? (int64_t)lds.load[r] : 0;
+    } else if (r < R) {
       for (int s = 0; s < S; ++s) v += slot[r * S + s].y;
+    }
     Lr[m] = v;
     mine += v;
   }
@@ -529,7 +596,7 @@ __device__ void plan_wave_body(const PlanDeviceLaunch& a, const PlanWaveLds& lds
   const bool active = N > 0 && bg.max_swaps > 0 && R > 1;
   bool small_done = false;
   if constexpr (RPL == 1) {
-    if (active && N < (int64_t)0x7fffffff && J == 1 && !timed) {
+    if (active && N < (int64_t)1 << 30 && J == 1 && !timed) {
       uint32_t Lu = (uint32_t)Lr[0];
       ns = rounds_small<CPL>(a, slot, part, Lu, g_num, g_den);
       Lr[0] = Lu;

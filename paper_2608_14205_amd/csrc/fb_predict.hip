@@ -543,7 +543,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   __shared__ __attribute__((aligned(16))) float gsc[GSC_TOK][kMaxGroups];
   __shared__ int32_t s_flag;
   __shared__ uint32_t s_marks;
-  __shared__ int64_t s_red[kWaves][2];
+  __shared__ int32_t s_stray;                     // an expert on a rank that does not exist
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1209,10 +1209,26 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   // ticket.  The workgroup that takes the last ticket therefore reads complete counters with its
   // own atomics.  This avoids an agent-scope fence per workgroup, which on gfx950 writes back and
   // invalidates the whole L2 and serialises across the workgroups.
+  // The tables that the last workgroup needs do not depend on the counts: every workgroup fetches
+  // them here, under the latency of its counter updates (E <= 256: thread e has expert e).
+  static_assert(EPAD <= kThreads, "one expert per thread");
+  constexpr int kPre = (wave_cap(1, 2) + kThreads - 1) / kThreads;   // R * S <= 704
+  const bool has_plan = p.plan_cpl != 0;
+  const int rs_plan = has_plan ? p.plan.R * p.plan.S : 0;
+  const bool timed = has_plan && p.plan.timed;
+  int32_t pre[kPre];
+#pragma unroll
+  for (int i = 0; i < kPre; ++i) {
+    const int c = tid + i * kThreads;
+    pre[i] = c < rs_plan ? p.plan.slot_expert[c] : -1;
+  }
+  const int my_rank = tid < E ? p.e2r[tid] : 0;
+  const int64_t my_bytes = timed && tid < E ? p.plan.expert_bytes[tid] : 0;
+  const int32_t my_node = timed && tid < p.plan.R ? p.plan.rank_node[tid] : 0;
   int done = 0;
-  for (int e = tid; e < E; e += kThreads) {
-    const int v = hist[e];
-    if (v) done |= atomicAdd(&p.ws_acc[e], v);
+  if (tid < E) {
+    const int v = hist[tid];
+    if (v) done = atomicAdd(&p.ws_acc[tid], v);
   }
   if (done < 0) s_flag = -1;                   // never true (counters stay below 2^31); uses the values
   __syncthreads();
@@ -1221,73 +1237,86 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   if (s_flag != 1) return;
 
   // ---- last workgroup: counts, rank fold, max/mean; leaves the workspace zeroed -------------
-  int32_t* rl = reinterpret_cast<int32_t*>(smem);
-  for (int r = tid; r < p.R; r += kThreads) rl[r] = 0;
-  if (tid == 0) s_flag = 0;
+  // A chain of latencies on the critical path of every pass, so nothing waits that need not: the
+  // planner's tables are checked and laid out while the counters are on their way, the barrier that
+  // publishes the counts starts the planner in wave 0, and wave 1 writes the fold beside it.
+  const int total = tid < E ? atomicExch(&p.ws_acc[tid], 0) : 0;
+  if (tid == 0) atomicExch(p.ws_ticket, 0u);
   // every workgroup is past its wait once the last ticket is taken: the arrival words go back to zero
   if constexpr (MODE != kFused)
     for (int i = tid; i < (int)(p.nblocks / (uint32_t)p.ks); i += kThreads) atomicExch(&p.ws_tile[i], 0u);
-  __syncthreads();
-  // the swap plan's tables are fetched while the counters are read, and go straight to the
-  // planner's LDS (its arrays lie past the rank loads at the start of smem); R * S <= 704 and E <= 256
-  static_assert(SMEM >= plan_wave_lds_bytes(wave_cap(1, 2), 1), "the planner's LDS fits");
+  constexpr size_t kPlanLds = (plan_wave_lds_bytes(wave_cap(1, 2), 1) + 15) / 16 * 16;
+  static_assert(SMEM >= kPlanLds + FB_MAX_RANKS * 4, "the planner's tables and the rank loads fit");
   const PlanWaveLds pl = plan_wave_lds(smem, wave_cap(1, 2), 1);
-  constexpr int kPre = (wave_cap(1, 2) + kThreads - 1) / kThreads;
-  const int rs_plan = p.plan_cpl != 0 ? p.plan.R * p.plan.S : 0;
-  int32_t pre[kPre];
+  int32_t* rl = reinterpret_cast<int32_t*>(smem + kPlanLds);
+  for (int r = tid; r < p.R; r += kThreads) rl[r] = 0;
+  if (tid == 0) { s_stray = 0; *pl.state = 0; }
+  if (has_plan) {
+    if (tid < E) pl.reps[tid] = 0;
+    if (tid < 64) { pl.load[tid] = 0; pl.part[tid] = 0; }
+  }
+  lds_barrier();
+  if (has_plan) {
+    // a plain placement holds every expert once; a replica (a value >= E) leaves the table to the
+    // planner's full check
+    int state = 0;
 #pragma unroll
-  for (int i = 0; i < kPre; ++i) {
-    const int c = tid + i * kThreads;
-    pre[i] = c < rs_plan ? p.plan.slot_expert[c] : 0;
-  }
-  const bool pre_bytes = p.plan_cpl != 0 && p.plan.timed && tid < E;
-  const int64_t preb = pre_bytes ? p.plan.expert_bytes[tid] : 0;
-  for (int e = tid; e < E; e += kThreads) {
-    const int v = atomicExch(&p.ws_acc[e], 0);
-    p.counts[e] = v;
-    if (p.plan_cpl != 0) pl.cnt[e] = v;
-    const int r = p.e2r[e];
-    if (r >= 0 && r < p.R) atomicAdd(&rl[r], v);
-    else s_flag = 1;
-  }
-#pragma unroll
-  for (int i = 0; i < kPre; ++i) {
-    const int c = tid + i * kThreads;
-    if (c < rs_plan) pl.vals[c] = pre[i];
-  }
-  if (pre_bytes) pl.ebytes[tid] = preb;
-  __syncthreads();
-  int64_t mx = 0, sum = 0;
-  for (int r = tid; r < p.R; r += kThreads) {
-    const int v = rl[r];
-    p.rank_loads[r] = v;
-    mx = v > mx ? v : mx;
-    sum += v;
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    const int64_t om = __shfl_xor(mx, off), os = __shfl_xor(sum, off);
-    mx = om > mx ? om : mx;
-    sum += os;
-  }
-  if (lane == 0) { s_red[wave][0] = mx; s_red[wave][1] = sum; }
-  __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < kWaves; ++w) {
-      mx = s_red[w][0] > mx ? s_red[w][0] : mx;
-      sum += s_red[w][1];
+    for (int i = 0; i < kPre; ++i) {
+      const int c = tid + i * kThreads;
+      if (c >= rs_plan) break;
+      const int v = pre[i];
+      pl.vals[c] = v;
+      if (v < -1) state |= kPlanBad;
+      else if (v >= E) state |= kPlanReplicas;
+      else if (v >= 0) { atomicAdd(&pl.reps[v], 1); pl.base[v] = c; }
+      else pl.slot[c] = make_uint2((uint32_t)(E + c), 0u);
     }
-    double ratio = sum == 0 ? 1.0 : (double)mx * (double)p.R / (double)sum;
-    *p.max_mean = s_flag ? -1.0 : ratio;
-    atomicExch(p.ws_ticket, 0u);
+    if (timed && tid < E) {
+      pl.ebytes[tid] = my_bytes;
+      if (my_bytes < 0 || my_bytes > kCostLimit) state |= kPlanBad;
+    }
+    lds_barrier();
+    if (tid < E) {
+      pl.cnt[tid] = total;
+      if (pl.reps[tid] != 1) state |= kPlanNotOnce;
+      else {                                   // base holds a slot of the table, whatever else is wrong
+        const int c = pl.base[tid];
+        pl.slot[c] = make_uint2((uint32_t)tid, (uint32_t)total);
+        atomicAdd(&pl.load[c / p.plan.S], (unsigned long long)(int64_t)total);
+      }
+      if (total < 0) state |= kPlanBad;
+    }
+    if (state) atomicOr(pl.state, state);
   }
-  if (p.plan_cpl != 0) {
-    // The swap plan of the counts just written (Alg. 1, frontier mode): the one-wave planner in
-    // this workgroup's first wave, in LDS the selection no longer needs, with its tables already
-    // there.  The barrier publishes every wave's entries; the other waves are done.
-    __syncthreads();
-    if (wave != 0) return;
-    if (p.plan_cpl == 1) plan_wave_body<1, 1, true>(p.plan, pl);
-    else plan_wave_body<1, 2, true>(p.plan, pl);
+  if (tid < E) {
+    p.counts[tid] = total;
+    if (my_rank >= 0 && my_rank < p.R) atomicAdd(&rl[my_rank], total);
+    else s_stray = 1;
+  }
+  lds_barrier();
+  if (wave == 1) {
+    int64_t mx = 0, sum = 0;
+    for (int r = lane; r < p.R; r += 64) {
+      const int v = rl[r];
+      p.rank_loads[r] = v;
+      mx = v > mx ? v : mx;
+      sum += v;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      const int64_t om = __shfl_xor(mx, off), os = __shfl_xor(sum, off);
+      mx = om > mx ? om : mx;
+      sum += os;
+    }
+    if (lane == 0) {
+      const double ratio = sum == 0 ? 1.0 : (double)mx * (double)p.R / (double)sum;
+      *p.max_mean = s_stray ? -1.0 : ratio;
+    }
+  }
+  if (has_plan && wave == 0) {
+    // The swap plan of the counts (Alg. 1, frontier mode): the one-wave planner in this workgroup's
+    // first wave, in LDS the selection no longer needs, with its tables already there.
+    if (p.plan_cpl == 1) plan_wave_body<1, 1, true>(p.plan, pl, my_node);
+    else plan_wave_body<1, 2, true>(p.plan, pl, my_node);
   }
 }
 

@@ -108,6 +108,35 @@ def test_device_planner_loads_beyond_31_bits(R):
         _same(host, ref)
 
 
+@pytest.mark.parametrize("R,S", [(2, 3), (3, 2), (17, 8), (64, 8), (64, 11)])
+@pytest.mark.parametrize("gamma", [None, (0, 1), (3, 7)])
+def test_frontier_rounds(R, S, gamma):
+    """The one-wave planner's short rounds at their edges: two and three ranks (no, then one, rank
+    outside the pair), ranks past a row of 16 lanes, more swaps than the 64 whose records wait in
+    the lanes, many ties, per-rank caps, and loads that sum to just below and just above 2^30."""
+    print(f"[plan] frontier rounds R={R} S={S} gamma={gamma}", flush=True)
+    g = np.random.default_rng(R * 16 + S)
+    E = R * S - R // 2                               # some empty slots
+    for it, top in enumerate((4, 60, 5000, 2 ** 31 // E - 1)):
+        cells = np.full(R * S, -1, np.int32)
+        cells[g.permutation(R * S)[:E]] = np.arange(E)
+        slots = cells.reshape(R, S)
+        counts = g.integers(0, top, size=E).astype(np.int32)
+        if it == 3:                                  # N just below, then at, 2^30
+            counts = (counts.astype(np.float64) * (2 ** 30 - 1) / counts.sum()).astype(np.int32)
+            counts[0] += 2 ** 30 - 1 - int(counts.sum())
+        for extra in ((0, 1) if it == 3 else (0,)):
+            counts[0] += extra
+            gm = (0, 1) if it == 3 else gamma        # the exact benefit fits 64 bits there only
+            for cap in (0, 3):
+                bg = fb.Budget(4 * R, per_rank_cap=cap, gamma=gm, tau=it)
+                host = fb.plan_swaps(counts, slots, bg)
+                _same(_dev(counts, slots, bg), host)
+                if R <= 17 and top < 100:
+                    _same(host, OP.plan_swaps(counts, slots, bg.max_swaps, gamma=bg.gamma, tau=bg.tau,
+                                              per_rank_cap=cap))
+
+
 def test_device_planner_reports_bad_placement():
     print("[plan] invalid slot table", flush=True)
     slots = np.array([[0, 1], [1, 3]], np.int32)   # expert 1 twice, expert 2 missing
