@@ -19,7 +19,7 @@
 //     L2-resident) straight into registers through a ring of 16 k-step slices, 15 k-steps ahead of
 //     the MFMAs; the hidden fragments are read from LDS one k-step ahead.  The router weight is the
 //     A operand (M = experts) and the hidden tile is B (N = tokens): v_mfma_f32_32x32x16_bf16 (or
-//     32x32x2 f32), so each lane ends with groups of four consecutive experts of one token.
+//     the same on split values for f32), so each lane ends with groups of four consecutive experts of one token.
 //   * One workgroup barrier per stage, placed before the stage's last k-step: it publishes the next
 //     stage (every wave waits for its own share of that stage's loads first) and frees the buffer
 //     just read, which the next load batch then refills.  Waits are counted, never drained.
@@ -43,6 +43,7 @@ namespace fb {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -311,7 +312,7 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   static_assert(kWaitStage <= 63 && (kRingW - 1) * FE + NS * LPW <= 63,
                 "more loads in flight than a wave can count");
   static_assert(LPW >= 1 && BM % (4 * kWaves) == 0, "stage loads split evenly over the waves");
-  static_assert(kRingW % kNStep == 0, "the weight ring holds whole stages");
+  static_assert(kRingW % kNStep == 0 && kNStep % 4 == 0, "the weight ring holds whole stages, a stage whole pairs of pairs of k-steps");
   const uint32_t lds0 = lds_addr(ring_lds);
   const int nst = p.nstages;
   const int Hb = p.Hbytes;
@@ -392,22 +393,61 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
 
   auto mma = [&](const u32x4(&a)[FE], const u32x4(&b)[FT]) {
 #pragma unroll
-    for (int ft = 0; ft < FT; ++ft) {
+    for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-      for (int fe = 0; fe < FE; ++fe) {
-        if constexpr (BF16) {
-          acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8, a[fe]), __builtin_bit_cast(bf16x8, b[ft]), acc[fe][ft], 0, 0, 0);
-        } else {
-          // four k-pairs per fragment; A and B take the same k for every lane
-          const f32x4 av = __builtin_bit_cast(f32x4, a[fe]);
-          const f32x4 bv = __builtin_bit_cast(f32x4, b[ft]);
+      for (int fe = 0; fe < FE; ++fe)
+        acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8, a[fe]), __builtin_bit_cast(bf16x8, b[ft]), acc[fe][ft], 0, 0, 0);
+  };
+  // float32 inputs: every value is the exact sum of three bf16 parts (its upper 16 bits, which no value
+  // overflows; the rest rounded to bf16, so that what is left has either sign; what is left, whose 8
+  // bits fit), and the product keeps the six part products above 2^-22 of it, on bf16 MFMAs with
+  // float32 accumulation.  Two k-steps (8 values of a lane) make one
+  // fragment; the MFMAs of a pair of k-steps run among the splitting of the next pair, half of them
+  // per k-step, so the vector ALU works beside the matrix cores.  Bound by the two in balance (E =
+  // 256: 96 vector and 12 matrix instructions per k-step and wave, 64 rows); the six products need
+  // 0.38 of the matrix time of v_mfma_f32_32x32x2_f32, which this replaced: E = 256, H = 7168, T =
+  // 20000 865 -> 450 us, T = 4096 with selections and logits written 143 -> 102, E = 64, H = 2048, T =
+  // 1000 25.4 -> 20.7.  The logits' error against 64 bits is smaller (fewer accumulations): 1.49e-6
+  // -> 1.35e-6 and 3.9e-7 -> 3.0e-7 of their norm at those two widths.
+  struct Parts { u32x4 v[3]; };
+  constexpr int kSplitOps = (FE + FT) * 22 + FE * 4;   // vector instructions of a k-step's splitting
+  Parts sa[2][FE], sb[2][FT];                    // [parity of the k-step pair]
+  if constexpr (!BF16) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc[fe][ft], 0, 0, 0);
-        }
-      }
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+      for (int fe = 0; fe < FE; ++fe) sa[1][fe].v[i] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) sb[1][ft].v[i] = u32x4{0u, 0u, 0u, 0u};
     }
+  }
+  // the parts of a lane's four values into dwords 2 half, 2 half + 1 of the fragments
+  auto split4 = [&](Parts& out, const u32x4& x, int half) {
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const uint32_t a = x[2 * w], b = x[2 * w + 1];
+      const float ra = __uint_as_float(a) - __uint_as_float(a & 0xFFFF0000u);
+      const float rb = __uint_as_float(b) - __uint_as_float(b & 0xFFFF0000u);
+      const uint32_t m = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
+      const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
+      out.v[0][2 * half + w] = __builtin_amdgcn_perm(b, a, 0x07060302u);       // upper halves
+      out.v[1][2 * half + w] = m;
+      out.v[2][2 * half + w] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
+    }
+  };
+  // three of the six part products of a pair of k-steps, smallest parts first
+  auto mma_parts = [&](const Parts(&a)[FE], const Parts(&b)[FT], int half) {
+    constexpr int kI[6] = {2, 0, 1, 1, 0, 0}, kJ[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+        for (int fe = 0; fe < FE; ++fe)
+          acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8, a[fe].v[kI[3 * half + i]]),
+              __builtin_bit_cast(bf16x8, b[ft].v[kJ[3 * half + i]]), acc[fe][ft], 0, 0, 0);
   };
 
   // ---- prologue: stages 0 .. NS-1 and k-steps 0 .. kRingW-2 in flight, then stage 0 published.
@@ -463,12 +503,30 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
         wait_w(q);                              // this k-step's weight slice
         pin(bq[q & 1]);
         pin_acc(ring[slot]);
-        mma(ring[slot], bq[q & 1]);
+        if constexpr (BF16) {
+          mma(ring[slot], bq[q & 1]);
+        } else {
+          const int par = (q >> 1) & 1;
+#pragma unroll
+          for (int fe = 0; fe < FE; ++fe) split4(sa[par][fe], ring[slot][fe], q & 1);
+#pragma unroll
+          for (int ft = 0; ft < FT; ++ft) split4(sb[par][ft], bq[q & 1][ft], q & 1);
+          mma_parts(sa[par ^ 1], sb[par ^ 1], q & 1);
+#pragma unroll
+          for (int i = 0; i < 3 * FE * FT; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, kSplitOps / (3 * FE * FT), 0);   // its vector share
+          }
+        }
         // keep every load in the k-step it was written in: the prefetch distances are the design
         __builtin_amdgcn_sched_barrier(0);
       }
       bi = bn;
     }
+  }
+  if constexpr (!BF16) {                         // the last pair of k-steps
+    mma_parts(sa[1], sb[1], 0);
+    mma_parts(sa[1], sb[1], 1);
   }
   // no stage load may still be writing LDS when the tile is reused below
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
@@ -1431,16 +1489,20 @@ int launch_cfg_bm(const PredictLaunch& a) {
     p.plan_cpl = (int64_t)a.plan->S * a.plan->S <= 64 ? 1 : 2;
   }
   hipStream_t st = static_cast<hipStream_t>(a.stream);
-  if (p.ks > 1) {
+  // a grid that leaves half of the CUs idle has half-height tiles where there are any
+  constexpr bool kSplits = EPAD != 256 || BM != TileCfg<EPAD>::BM;
+  if (kSplits && p.ks > 1) {
     p.nblocks = (uint32_t)(tiles * p.ks);
-    if constexpr (can_share(EPAD)) {
+    if constexpr (kSplits && can_share(EPAD)) {
       if (shares(EPAD, p.ks))
         hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kShare>), dim3(p.nblocks), dim3(kThreads),
                            0, st, p);
     }
-    if (!shares(EPAD, p.ks))
-      hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kSplit>), dim3(p.nblocks), dim3(kThreads),
-                         0, st, p);
+    if constexpr (kSplits) {
+      if (!shares(EPAD, p.ks))
+        hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kSplit>), dim3(p.nblocks), dim3(kThreads),
+                           0, st, p);
+    }
   } else {
     hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kFused>), dim3(p.nblocks), dim3(kThreads),
                        0, st, p);

@@ -459,6 +459,30 @@ def test_split_slices(E, T, H, dtype):
         assert not pred.workspace[:2048].cpu().numpy().any()
 
 
+@pytest.mark.parametrize("E,H,T,scale", [(16, 64, 40, 1.0), (200, 272, 130, 2.0 ** 60), (256, 1040, 70, 2.0 ** -60)])
+def test_f32_values(E, H, T, scale):
+    """float32 logits of values with full mantissas, widely spread exponents and either sign against
+    float64.  Each value is exactly h + m + l with |m| <= 2^-7 |x| (the rest of truncating to 8 bits)
+    and |l| <= 2^-16 |x| (that rest rounded to 8 bits), so the products left out, m l', l m' and l l',
+    are below 2^-21.9 |x w|; the six kept are added in 6 H / 16 float32 accumulations."""
+    _say(f"[f32] E={E} H={H} T={T} scale={scale}")
+    g = np.random.default_rng(E)
+    x = (g.standard_normal((T, H)) * np.exp2(g.integers(-12, 13, (T, H))) * scale).astype(np.float32)
+    w = (g.standard_normal((E, H)) * np.exp2(g.integers(-12, 13, (E, H)))).astype(np.float32)
+    x[0], x[1, ::2] = 0.0, np.float32(3.4e38) * np.float32(2.0 ** -8) if scale == 1.0 else 0.0
+    if scale == 1.0:
+        w *= np.float32(2.0 ** -20)
+    out = fb.Predictor().predict_load(to_device(x, "f32"), fb.pack_router_weight(to_device(w, "f32")),
+                                      fb.Scoring("softmax", 2), torch.zeros(E, dtype=torch.int32, device="cuda"), 1,
+                                      return_topk=True, return_logits=True)
+    torch.cuda.synchronize()
+    ref = x.astype(np.float64) @ w.astype(np.float64).T
+    mag = np.abs(x).astype(np.float64) @ np.abs(w).astype(np.float64).T
+    bound = (2.0 ** -21.9 + (6 * H / 16 + 24) * 2.0 ** -24) * mag
+    err = np.abs(out.logits.cpu().numpy() - ref)
+    assert (err <= bound).all(), float((err / np.maximum(bound, 1e-300)).max())
+
+
 def test_qwen3_layers_back_to_back():
     """Qwen3-MoE-shaped layers (every token against the oracle) and the device plan of each layer's
     counts under the config's budget against the oracle's plan.  All 48 layers run in bench.py's
