@@ -223,9 +223,11 @@ int fb_predict_load(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,
  *                        too small to occupy the GPU runs in split mode: the hidden dimension of
  *                        every tile is split over several workgroups whose partial logits (kept
  *                        in the workspace past its first 2048 bytes) are added in a fixed order,
- *                        still in one launch.  Results are then deterministic and within the
- *                        float32 summation-order tolerance of the fused path's.  With less room
- *                        the batch runs in fewer splits, down to the fused path.
+ *                        still in one launch.  A batch of more than 128 experts whose tiles
+ *                        do not fill their last round of workgroups runs those tiles the same
+ *                        way, in a second launch.  Results are then deterministic and within
+ *                        the float32 summation-order tolerance of the fused path's.  With less
+ *                        room the batch runs in fewer splits, down to the fused path.
  * Every other argument, and every error, as in fb_predict_load. */
 int fb_predict_load_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,
                            int32_t dtype, const void* router_packed, size_t router_packed_bytes,

@@ -97,7 +97,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int32_t* wsum) {
 // 0 of *bad.  On return, after a barrier, reps[e] = c_e, *jmax = the largest c_e, and ej[c] =
 // (j << 12) | e for the replica in slot c (-1 for an empty or invalid slot; E <= 4096).
 template <int NT>
-__device__ void check_placement(int E, int R, int S, const int32_t* vals, const int32_t* cnt,
+__device__ __forceinline__ void check_placement(int E, int R, int S, const int32_t* vals, const int32_t* cnt,
                                 int32_t* ej, int32_t* reps, int32_t* base, int32_t* flag,
                                 int32_t* wsum, int32_t* bad, int32_t* jmax) {
   const int tid = threadIdx.x;
@@ -484,7 +484,7 @@ __device__ __forceinline__ PlanWaveLds plan_wave_lds(char* mem, int CAP, int RPL
 // Eq. 9 on their link, admitted if it fits what is left of both ranks' and of the link's budgets,
 // and the round's best is the largest benefit / cost, then the tie key.
 template <int RPL, int CPL, bool PREPARED = false>
-__device__ void plan_wave_body(const PlanDeviceLaunch& a, const PlanWaveLds& lds, int32_t node_in = 0) {
+__device__ __forceinline__ void plan_wave_body(const PlanDeviceLaunch& a, const PlanWaveLds& lds, int32_t node_in = 0) {
   int32_t* const vals = lds.vals;      // the input tables
   int32_t* const cnt = lds.cnt;
   int32_t* const ej = lds.ej;

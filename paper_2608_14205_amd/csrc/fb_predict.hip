@@ -98,7 +98,8 @@ struct Params {
   uint32_t* ws_tile;   // split mode: arrival word per tile (kSplit)
   int32_t* topk_idx;
   float* logits;
-  uint32_t nblocks;    // workgroups of the launch, and the tickets the last one completes
+  uint32_t tickets;    // workgroups that count (of both launches where a batch takes two)
+  uint32_t full;       // split mode: tiles before the first split one, contracted whole by a launch before
   int32_t nstages;     // stages this workgroup contracts
   int32_t st_base;     // first of them
   int32_t st_total;    // stages of a whole row
@@ -314,7 +315,10 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   static_assert(LPW >= 1 && BM % (4 * kWaves) == 0, "stage loads split evenly over the waves");
   static_assert(kRingW % kNStep == 0 && kNStep % 4 == 0, "the weight ring holds whole stages, a stage whole pairs of pairs of k-steps");
   const uint32_t lds0 = lds_addr(ring_lds);
-  const int nst = p.nstages;
+  // wave-uniform; readfirstlane keeps them, and the offsets and the descriptor of the weight loads
+  // derived from them, in scalar registers
+  const int nst = __builtin_amdgcn_readfirstlane(p.nstages);
+  const int st_base = __builtin_amdgcn_readfirstlane(p.st_base);
   const int Hb = p.Hbytes;
   const int64_t rows = (p.T - row0) < BM ? (p.T - row0) : BM;
 
@@ -338,7 +342,7 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   // slices: the scheduling barriers keep other loads from moving into or across it.
   auto load_stage = [&](int bi, int st) {        // bi: stage buffer (wave-uniform)
     const bool live = st < nst;
-    const int sb = live ? (p.st_base + st) * kStageRowBytes : 0;
+    const int sb = live ? (st_base + st) * kStageRowBytes : 0;
     const int lim = live ? Hb - sb : 0;           // bytes of the stage inside the row (scalar)
     char* const dst = ring_lds + bi * STAGE + wave * LPW * 1024;
     __builtin_amdgcn_sched_barrier(0);
@@ -357,15 +361,16 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   // known exactly, where the compiler's own tracking turns conservative at the loop head.
   constexpr int kPackStage = EPAD * kStageRowBytes;
   const uint64_t wbase_addr = reinterpret_cast<uint64_t>(p.wpack);
-  const i32x4 wr = {(int32_t)(uint32_t)wbase_addr, (int32_t)(uint32_t)(wbase_addr >> 32),
-                    p.st_total * kPackStage, (int32_t)kRsrcWord3};
+  const i32x4 wr = {__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)wbase_addr),
+                    __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(wbase_addr >> 32)),
+                    __builtin_amdgcn_readfirstlane(p.st_total * kPackStage), (int32_t)kRsrcWord3};
   const uint32_t wbase = (uint32_t)(we * kNStep * FE * 1024 + lane * 16);
   auto load_w = [&](u32x4(&dst)[FE], int st, int q) {
     const bool ok = st < nst;
 #pragma unroll
     for (int fe = 0; fe < FE; ++fe)
       buffer_load_b128_acc(dst[fe], wr, ok ? wbase + (uint32_t)((q * FE + fe) * 1024) : kOobOffset,
-                           ok ? (p.st_base + st) * kPackStage : 0);
+                           ok ? (st_base + st) * kPackStage : 0);
   };
   // loads issued after the weight slice of k-step q (of any stage) by the time its MFMAs start: the
   // slices of the next kRingW - 1 k-steps, and the stage batches issued at k-step 7 of the stages
@@ -555,8 +560,9 @@ __device__ __forceinline__ f32x4 partial_load(const __amdgpu_buffer_rsrc_t& rsrc
 }
 
 // Polls of a tile's arrival word before a workgroup gives its slice to the tile's last arrival: each
-// takes about 0.7 us, so some 50 us, several times the spread of one launch's workgroups.
-constexpr int kArrivalPolls = 64;
+// is a trip to memory (0.2 us or more), so at least 50 us in all, several times the spread of one
+// launch's workgroups.
+constexpr int kArrivalPolls = 256;
 // Arrival word of a tile: arrivals in the low half, given-up slices (one bit per split) in the high.
 constexpr uint32_t kArrivalMask = 0xFFFFu;
 static_assert(kMaxSplits <= 16, "one given-up bit per split in the arrival word");
@@ -610,9 +616,11 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int we = wave % WE;
   const int wt = wave / WE;
-  const int tile = MODE != kFused ? (int)(blockIdx.x / (uint32_t)p.ks) : (int)blockIdx.x;
-  const int split = MODE != kFused ? (int)(blockIdx.x % (uint32_t)p.ks) : 0;
-  const int chunk = MODE != kFused ? (p.st_total + p.ks - 1) / p.ks : p.st_total;   // stages per split
+  const int split_tile = MODE != kFused ? __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (uint32_t)p.ks)) : 0;
+  const int tile = MODE != kFused ? (int)p.full + split_tile : (int)blockIdx.x;
+  const int split = MODE != kFused ? (int)blockIdx.x - split_tile * p.ks : 0;
+  // stages per split
+  const int chunk = MODE != kFused ? __builtin_amdgcn_readfirstlane((p.st_total + p.ks - 1) / p.ks) : p.st_total;
   const int64_t row0 = (int64_t)tile * BM;
   const int E = p.E;
 
@@ -652,7 +660,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   uint32_t taken = 1;                              // slices this workgroup finishes, one bit each
   if constexpr (MODE != kFused)
     pr = __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<char*>(p.partial) +
-                                                   (size_t)tile * p.ks * kBlockBytes),
+                                                   (size_t)split_tile * p.ks * kBlockBytes),
                                            (short)0, p.ks * kBlockBytes, kRsrcWord3);
   if constexpr (MODE == kSplit) {
     // The tile's last split to arrive adds the partials and finishes the whole tile.  16 bytes are four experts of one token, at unit
@@ -673,7 +681,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
     __syncthreads();
-    if (tid == 0) s_flag = atomicAdd(&p.ws_tile[tile], 1u) == (uint32_t)p.ks - 1 ? 1 : 0;
+    if (tid == 0) s_flag = atomicAdd(&p.ws_tile[split_tile], 1u) == (uint32_t)p.ks - 1 ? 1 : 0;
     __syncthreads();
     if (s_flag != 1) return;
     taken = (1u << p.ks) - 1u;
@@ -729,7 +737,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
     __syncthreads();
     if (tid == 0) {
-      const uint32_t old = atomicAdd(&p.ws_tile[tile], 1u);
+      const uint32_t old = atomicAdd(&p.ws_tile[split_tile], 1u);
       int state = 0;                               // 1: every split has arrived
       uint32_t marks = 0;
       if ((old & kArrivalMask) == (uint32_t)p.ks - 1) {
@@ -737,7 +745,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
         marks = old >> 16;
       }
       for (int i = 0; state == 0 && i < kArrivalPolls; ++i) {
-        const uint32_t v = __hip_atomic_load(&p.ws_tile[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t v = __hip_atomic_load(&p.ws_tile[split_tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         state = (v & kArrivalMask) == (uint32_t)p.ks ? 1 : 0;
         __builtin_amdgcn_s_sleep(1);
       }
@@ -757,7 +765,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
       __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
       __syncthreads();
       if (tid == 0)
-        s_flag = (atomicOr(&p.ws_tile[tile], 0x10000u << split) & kArrivalMask) == (uint32_t)p.ks ? 1 : 0;
+        s_flag = (atomicOr(&p.ws_tile[split_tile], 0x10000u << split) & kArrivalMask) == (uint32_t)p.ks ? 1 : 0;
       __syncthreads();
       if (s_flag == 0) return;
     }
@@ -803,7 +811,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
     // the reciprocal dominate this phase, and it then needs only three other operations per
     // score.  A sigmoid score is never -0 (the reciprocal is positive, and +0 + -0 = +0), so only
     // the logits need the -0 -> +0 canonicalisation of the order-preserving key.
-    auto emit = [&](auto sig_c, auto lbias_c, auto groups_c) {
+    auto emit = [&](auto sig_c, auto lbias_c, auto groups_c) __attribute__((always_inline)) {
       constexpr bool SIG = decltype(sig_c)::value, LBIAS = decltype(lbias_c)::value;
       constexpr bool GROUPS = decltype(groups_c)::value;
       // top two scores of each (expert block, token block) over this lane's 16 of its 32 experts
@@ -893,7 +901,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   // G lanes per token; lane jg holds 32 keys; element i of the lane is expert
   // 32 L + 4 ((i / 4 + L) mod 8) + i mod 4 (L = the lane's 32-expert slice).
   auto finish = [&](auto g_c, int jg, int tlu, bool tv, int64_t ttu, const uint32_t(&key)[32],
-                    const float(&sv)[32], int L) {
+                    const float(&sv)[32], int L) __attribute__((always_inline)) {
     constexpr int G = decltype(g_c)::value;
     // per-lane cache of the kCache largest keys (descending), refilled by a rescan below the last
     // popped key when it runs dry
@@ -993,7 +1001,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   };
   // split mode: the sum of the partials of tokens [t0, t0 + nt) and their scores, into rows 0 .. nt - 1
   // of the score tile.  own: the split whose partials those rows already hold, -1 for none.
-  auto sum_slice = [&](auto sig_c, auto lbias_c, auto units_c, int t0, int nt, int own) {
+  auto sum_slice = [&](auto sig_c, auto lbias_c, auto units_c, int t0, int nt, int own) __attribute__((always_inline)) {
     constexpr bool SIG = decltype(sig_c)::value, LBIAS = decltype(lbias_c)::value;
     constexpr int kU = decltype(units_c)::value;   // units per thread and splits per batch of loads
     constexpr int kJ = 16 / kU;
@@ -1056,11 +1064,13 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
     nt = slice_begin(sl + 1, BM, p.ks) - t0;
     using T1 = std::integral_constant<bool, true>;
     using F0 = std::integral_constant<bool, false>;
-    // a slice that gives every thread one unit has up to 16 splits: all of them in one batch of loads
+    // the smaller the slice, the more splits share the tile: all of them in one or two batches of loads
     using U4 = std::integral_constant<int, 4>;
+    using U2 = std::integral_constant<int, 2>;
     using U1 = std::integral_constant<int, 1>;
-    auto sum_by = [&](auto sig_c, auto lbias_c) {
+    auto sum_by = [&](auto sig_c, auto lbias_c) __attribute__((always_inline)) {
       if (nt * (EPAD / 4) <= kThreads) sum_slice(sig_c, lbias_c, U1{}, t0, nt, own);
+      else if (nt * (EPAD / 4) <= 2 * kThreads) sum_slice(sig_c, lbias_c, U2{}, t0, nt, own);
       else sum_slice(sig_c, lbias_c, U4{}, t0, nt, own);
     };
     if (p.kind == FB_SIGMOID) {
@@ -1290,7 +1300,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   }
   if (done < 0) s_flag = -1;                   // never true (counters stay below 2^31); uses the values
   __syncthreads();
-  if (tid == 0) s_flag = (atomicAdd(p.ws_ticket, (uint32_t)tickets) == p.nblocks - (uint32_t)tickets) ? 1 : 0;
+  if (tid == 0) s_flag = (atomicAdd(p.ws_ticket, (uint32_t)tickets) == p.tickets - (uint32_t)tickets) ? 1 : 0;
   __syncthreads();
   if (s_flag != 1) return;
 
@@ -1302,7 +1312,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   if (tid == 0) atomicExch(p.ws_ticket, 0u);
   // every workgroup is past its wait once the last ticket is taken: the arrival words go back to zero
   if constexpr (MODE != kFused)
-    for (int i = tid; i < (int)(p.nblocks / (uint32_t)p.ks); i += kThreads) atomicExch(&p.ws_tile[i], 0u);
+    for (int i = tid; i < (int)((p.tickets - p.full) / (uint32_t)p.ks); i += kThreads) atomicExch(&p.ws_tile[i], 0u);
   constexpr size_t kPlanLds = (plan_wave_lds_bytes(wave_cap(1, 2), 1) + 15) / 16 * 16;
   static_assert(SMEM >= kPlanLds + FB_MAX_RANKS * 4, "the planner's tables and the rank loads fit");
   const PlanWaveLds pl = plan_wave_lds(smem, wave_cap(1, 2), 1);
@@ -1387,19 +1397,18 @@ int epad_of(int32_t E) {
   return E <= 32 ? 32 : E <= 64 ? 64 : E <= 128 ? 128 : 256;
 }
 
-// Split mode: when the tiles would occupy at most half of the CUs, the stage range of every tile
-// is split over several workgroups, so that more CUs stream the hidden rows and each streams a share
-// of the router weight.  `room`: bytes for the partials.
+// Split mode: when `tiles` workgroups would occupy at most half of the CUs, the stage range of every
+// tile is split over several workgroups, so that more CUs stream the hidden rows and each streams a
+// share of the router weight.  `room`: bytes for the partials.
 //   * At least four stages per split (two where 16 splits are allowed): below that the first loads'
 //     latency is most of a split's time (E = 128, H = 2048, T = 1000: 19.8 us with 2 splits of 4
 //     stages, 23.0 us with 4 of 2).
 //   * Up to 8 splits, 16 for at most four 256-expert tiles.  E = 256, H = 7168, per pass with its
 //     plan, 4 / 8 / 16 splits: T = 64 39.1 / 33.5 / 31.7 us, T = 192 38.6 / 34.0 / 32.4, T = 500
 //     38.5 / 34.4 / 35.5, T = 1237 39.7 / 39.1 / 39.6.
-int split_count(int64_t T, int BM, int epad, int st_total, int num_cus, size_t room) {
-  const int64_t tiles = (T + BM - 1) / BM;
-  // split mode: at most half of the CUs hold tiles, and each tile has an arrival word
-  if (T <= 0 || tiles * 2 > num_cus || tiles > kMaxSplitTiles) return 1;
+int split_count(int64_t tiles, int BM, int epad, int st_total, int num_cus, size_t room) {
+  // at most half of the CUs hold tiles, and each tile has an arrival word
+  if (tiles <= 0 || tiles * 2 > num_cus || tiles > kMaxSplitTiles) return 1;
   const bool few = epad == 256 && tiles <= 4 && st_total >= 2 * kMaxSplits;
   int64_t ks = num_cus / tiles;
   const int64_t most = few ? kMaxSplits : st_total / 4 < 8 ? st_total / 4 : 8;
@@ -1417,25 +1426,50 @@ int split_count(int64_t T, int BM, int epad, int st_total, int num_cus, size_t r
 constexpr bool can_share(int epad) { return epad == 256; }
 bool shares(int epad, int ks) { return can_share(epad) && ks >= 4; }
 
-// Tile height of a launch (see launch_cfg).
-template <int EPAD>
-int tile_rows(int64_t T, int num_cus) {
-  constexpr int BM = TileCfg<EPAD>::BM;
-  if (EPAD == 256) {
-    const int64_t half_tiles = (T + BM / 2 - 1) / (BM / 2);
-    if (T > 0 && half_tiles <= num_cus) return BM / 2;
+// Tiles of a batch: tile height, tiles, how many of them are contracted whole, and the splits of the
+// ones after those (1: there are none).
+struct BatchShape {
+  int bm;
+  int64_t tiles, full;
+  int ks;
+};
+
+BatchShape shape_with(int bm, int epad, int64_t T, int st_total, int num_cus, size_t room) {
+  BatchShape s{bm, (T + bm - 1) / bm, 0, 1};
+  if (s.tiles <= num_cus) {
+    s.ks = split_count(s.tiles, bm, epad, st_total, num_cus, room);
+  } else if (can_share(epad)) {
+    // A 256-expert tile takes a CU (LDS and registers), so the tiles past a whole number of rounds
+    // would be a round of their own on a few CUs: they follow as a launch in split mode instead, and
+    // both launches add to the same counters and tickets.  E = 256, H = 7168, with the plan, round of
+    // their own / split launch: T = 33000 214 / 154 us, T = 36000 220 / 167, T = 40000 223 / 181, T =
+    // 48000 (two splits) 229 / 210.  One kernel with both kinds of workgroups saved the second launch
+    // but ran its whole tiles 8% slower (117 instead of 108 us to the end of the contraction).
+    s.ks = split_count(s.tiles % num_cus, bm, epad, st_total, num_cus, room);
+    s.full = s.tiles - s.tiles % num_cus;
   }
-  return BM;
+  if (s.ks == 1) s.full = s.tiles;
+  return s;
+}
+
+// Shape of a batch of T tokens with rows of st_total stages and `room` bytes for partials.
+template <int EPAD>
+BatchShape batch_shape(int64_t T, int st_total, int num_cus, size_t room) {
+  constexpr int BM = TileCfg<EPAD>::BM;
+  if constexpr (EPAD == 256) {
+    // Half-height tiles when the full-height grid would leave CUs idle and the half-height one still
+    // fits in a single round of workgroups: every CU then streams the weight for fewer tokens.
+    const BatchShape h = shape_with(BM / 2, EPAD, T, st_total, num_cus, room);
+    if (T > 0 && h.tiles <= num_cus) return h;
+  }
+  return shape_with(BM, EPAD, T, st_total, num_cus, room);
 }
 
 template <int EPAD>
 size_t split_bytes_cfg(int64_t T, int32_t H, int32_t dtype, int num_cus) {
-  const int BM = tile_rows<EPAD>(T, num_cus);
   const int st_total = (H * (dtype == FB_BF16 ? 2 : 4) + kStageRowBytes - 1) / kStageRowBytes;
-  const int ks = split_count(T, BM, EPAD, st_total, num_cus, SIZE_MAX);
-  if (ks <= 1) return 0;
-  const int64_t tiles = (T + BM - 1) / BM;
-  return (size_t)tiles * ks * BM * EPAD * sizeof(float);
+  const BatchShape s = batch_shape<EPAD>(T, st_total, num_cus, SIZE_MAX);
+  return (size_t)(s.tiles - s.full) * s.ks * s.bm * EPAD * sizeof(float);
 }
 
 template <int EPAD>
@@ -1450,7 +1484,7 @@ int launch_pack_cfg(const void* w, int32_t E, int32_t Hbytes, void* out, void* s
 }
 
 template <bool BF16, int EPAD, int BM>
-int launch_cfg_bm(const PredictLaunch& a) {
+int launch_cfg_bm(const PredictLaunch& a, const BatchShape& shape) {
   const int elem = BF16 ? 2 : 4;
   Params p;
   p.x = static_cast<const char*>(a.hidden);
@@ -1476,12 +1510,14 @@ int launch_cfg_bm(const PredictLaunch& a) {
   p.ws_tile = reinterpret_cast<uint32_t*>(static_cast<char*>(a.workspace) + kWsTileTicketOffset);
   p.topk_idx = a.topk_idx;
   p.logits = a.logits;
-  const int64_t tiles = (a.T + BM - 1) / BM;
-  p.nblocks = (uint32_t)(tiles > 0 ? tiles : 1);
+  const int64_t split_blocks = (shape.tiles - shape.full) * shape.ks;
+  const int64_t full_blocks = shape.tiles > 0 ? shape.full : 1;
+  p.full = (uint32_t)shape.full;
+  p.tickets = (uint32_t)(full_blocks + split_blocks);
   p.st_total = (p.Hbytes + kStageRowBytes - 1) / kStageRowBytes;
   p.nstages = p.st_total;
   p.st_base = 0;
-  p.ks = a.partial != nullptr ? split_count(a.T, BM, EPAD, p.st_total, a.num_cus, a.partial_bytes) : 1;
+  p.ks = shape.ks;
   p.partial = a.partial;
   p.plan_cpl = 0;
   if (a.plan != nullptr) {
@@ -1489,23 +1525,19 @@ int launch_cfg_bm(const PredictLaunch& a) {
     p.plan_cpl = (int64_t)a.plan->S * a.plan->S <= 64 ? 1 : 2;
   }
   hipStream_t st = static_cast<hipStream_t>(a.stream);
-  // a grid that leaves half of the CUs idle has half-height tiles where there are any
-  constexpr bool kSplits = EPAD != 256 || BM != TileCfg<EPAD>::BM;
-  if (kSplits && p.ks > 1) {
-    p.nblocks = (uint32_t)(tiles * p.ks);
-    if constexpr (kSplits && can_share(EPAD)) {
-      if (shares(EPAD, p.ks))
-        hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kShare>), dim3(p.nblocks), dim3(kThreads),
-                           0, st, p);
+  const dim3 block(kThreads), split_grid((unsigned)split_blocks);
+  if (full_blocks > 0)
+    hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kFused>), dim3((unsigned)full_blocks), block, 0, st, p);
+  if (split_blocks > 0) {
+    if constexpr (can_share(EPAD)) {
+      // (full-height tiles split only past whole rounds)
+      if (shares(EPAD, p.ks) || BM == TileCfg<EPAD>::BM)
+        hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kShare>), split_grid, block, 0, st, p);
     }
-    if constexpr (kSplits) {
+    if constexpr (!can_share(EPAD) || BM != TileCfg<EPAD>::BM) {
       if (!shares(EPAD, p.ks))
-        hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kSplit>), dim3(p.nblocks), dim3(kThreads),
-                           0, st, p);
+        hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kSplit>), split_grid, block, 0, st, p);
     }
-  } else {
-    hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kFused>), dim3(p.nblocks), dim3(kThreads),
-                       0, st, p);
   }
   return hipGetLastError() == hipSuccess ? FB_OK : FB_EDEVICE;
 }
@@ -1513,12 +1545,12 @@ int launch_cfg_bm(const PredictLaunch& a) {
 template <bool BF16, int EPAD>
 int launch_cfg(const PredictLaunch& a) {
   constexpr int BM = TileCfg<EPAD>::BM;
-  // Half-height tiles when the full-height grid would leave CUs idle and the half-height one still
-  // fits in a single wave of workgroups: every CU then streams the weight for fewer tokens.
+  const int st_total = (a.H * (BF16 ? 2 : 4) + kStageRowBytes - 1) / kStageRowBytes;
+  const BatchShape s = batch_shape<EPAD>(a.T, st_total, a.num_cus, a.partial != nullptr ? a.partial_bytes : 0);
   if constexpr (EPAD == 256) {
-    if (tile_rows<EPAD>(a.T, a.num_cus) == BM / 2) return launch_cfg_bm<BF16, EPAD, BM / 2>(a);
+    if (s.bm == BM / 2) return launch_cfg_bm<BF16, EPAD, BM / 2>(a, s);
   }
-  return launch_cfg_bm<BF16, EPAD, BM>(a);
+  return launch_cfg_bm<BF16, EPAD, BM>(a, s);
 }
 
 template <bool BF16>

@@ -483,6 +483,32 @@ def test_f32_values(E, H, T, scale):
     assert (err <= bound).all(), float((err / np.maximum(bound, 1e-300)).max())
 
 
+# one token past a whole round (16 splits), 65 tiles past it (two splits), a round and a half in f32
+@pytest.mark.parametrize("T,H,dtype", [(32769, 4096, "bf16"), (32768 + 64 * 128 + 5, 1024, "bf16"),
+                                       (32768 + 100, 528, "f32")])
+def test_tiles_past_a_whole_round(T, H, dtype):
+    """256-expert batches whose tiles past a whole round of workgroups run as a second launch in split
+    mode: oracle parity on every token, bit-identical repeats, a clean workspace header, and the same
+    prediction with no room for partials (one launch) where both match the oracle."""
+    wl = dataclasses.replace(CONFIGS["dsv3"].with_T(T), H=H, dtype=dtype)
+    _, e2r = contiguous_placement(wl.E, wl.R, wl.S)
+    need = fb.predict_split_workspace_bytes(T, wl.E, H, torch.bfloat16 if dtype == "bf16" else torch.float32)
+    _say(f"[tail] T={T} H={H} {dtype} workspace {need}")
+    assert need > 2048
+    li = make_layer(wl, 3)
+    pred = fb.Predictor()
+    a = run_gpu(li, wl, e2r, predictor=pred, packed=True)
+    stats = check_prediction(a, li, wl, e2r, label=f"tail T={T}")
+    check_counts_consistent(a, wl, e2r)
+    b = run_gpu(li, wl, e2r, predictor=pred, packed=True)
+    for key in ("counts", "rank_loads", "topk"):
+        assert np.array_equal(a[key], b[key]), key
+    assert not pred.workspace[:2048].cpu().numpy().any()
+    one = run_gpu(li, wl, e2r, predictor=fb.Predictor(split=False), packed=True)
+    if stats["mismatch"] == 0 and check_prediction(one, li, wl, e2r, label=f"one launch T={T}")["mismatch"] == 0:
+        assert np.array_equal(a["counts"], one["counts"])
+
+
 def test_qwen3_layers_back_to_back():
     """Qwen3-MoE-shaped layers (every token against the oracle) and the device plan of each layer's
     counts under the config's budget against the oracle's plan.  All 48 layers run in bench.py's
