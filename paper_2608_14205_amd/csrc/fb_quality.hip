@@ -26,29 +26,53 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 }
 
 // One token per thread: the predicted experts become a bit set, the actual ones are looked up.
+// Bound by latency at the sizes of one layer: a thread's first eight ids of both lists are fetched
+// before any is used (one trip to memory instead of one per id), and the workgroups' sums meet in
+// *hits, zeroed before the launch, with the arrivals counted above bit kHitsBits (T * k < 2^48), so
+// that the last one writes the sum and the rate with no launch of their own.  T = 8190, k = 6: 4.9 us
+// as before, the rate's launch of 1.3 us and its gap gone.
+constexpr int kHitsBits = 48;
+constexpr int kHitsBlocks = 1024;                // arrivals stay below 2^15
+constexpr int kIds = 8;                          // ids fetched together
 __global__ __launch_bounds__(kQThreads) void hits_kernel(const int32_t* __restrict__ pred,
                                                          const int32_t* __restrict__ act, int64_t T,
-                                                         int32_t k, unsigned long long* __restrict__ hits) {
+                                                         int32_t k, unsigned long long* __restrict__ hits,
+                                                         double* __restrict__ rate) {
   __shared__ unsigned long long s_part[kQWaves];
-  const int64_t t = blockIdx.x * (int64_t)kQThreads + threadIdx.x;
   unsigned long long h = 0;
-  if (t < T) {
+  for (int64_t t = blockIdx.x * (int64_t)kQThreads + threadIdx.x; t < T; t += (int64_t)gridDim.x * kQThreads) {
+    const int32_t* p = pred + t * k;
+    const int32_t* q = act + t * k;
     uint32_t bits[FB_MAX_EXPERTS / 32];
 #pragma unroll
     for (int w = 0; w < FB_MAX_EXPERTS / 32; ++w) bits[w] = 0;
-    for (int j = 0; j < k; ++j) {
-      const uint32_t e = (uint32_t)pred[t * k + j];
-      if (e < FB_MAX_EXPERTS) {
+    uint32_t ip[kIds], iq[kIds];
+    auto fetch = [&](uint32_t(&id)[kIds], const int32_t* from, int j0) {
 #pragma unroll
-        for (int w = 0; w < FB_MAX_EXPERTS / 32; ++w) bits[w] |= (w == (int)(e >> 5)) ? 1u << (e & 31) : 0u;
-      }
+      for (int j = 0; j < kIds; ++j) id[j] = j0 + j < k ? (uint32_t)from[j0 + j] : FB_MAX_EXPERTS;
+    };
+    fetch(ip, p, 0);
+    fetch(iq, q, 0);
+    for (int j0 = 0;;) {
+#pragma unroll
+      for (int j = 0; j < kIds; ++j)
+#pragma unroll
+        for (int w = 0; w < FB_MAX_EXPERTS / 32; ++w) bits[w] |= (w == (int)(ip[j] >> 5)) ? 1u << (ip[j] & 31) : 0u;
+      j0 += kIds;
+      if (j0 >= k) break;
+      fetch(ip, p, j0);
     }
-    for (int j = 0; j < k; ++j) {
-      const uint32_t e = (uint32_t)act[t * k + j];
-      uint32_t word = 0;
+    for (int j0 = 0;;) {
 #pragma unroll
-      for (int w = 0; w < FB_MAX_EXPERTS / 32; ++w) word = (w == (int)(e >> 5)) ? bits[w] : word;
-      h += (e < FB_MAX_EXPERTS) && ((word >> (e & 31)) & 1u);
+      for (int j = 0; j < kIds; ++j) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int w = 0; w < FB_MAX_EXPERTS / 32; ++w) word = (w == (int)(iq[j] >> 5)) ? bits[w] : word;
+        h += (word >> (iq[j] & 31)) & 1u;
+      }
+      j0 += kIds;
+      if (j0 >= k) break;
+      fetch(iq, q, j0);
     }
   }
 #pragma unroll
@@ -58,71 +82,87 @@ __global__ __launch_bounds__(kQThreads) void hits_kernel(const int32_t* __restri
   if (threadIdx.x == 0) {
     unsigned long long sum = 0;
     for (int w = 0; w < kQWaves; ++w) sum += s_part[w];
-    if (sum) atomicAdd(hits, sum);
+    const unsigned long long all = atomicAdd(hits, (1ull << kHitsBits) | sum) + sum;
+    if ((all >> kHitsBits) == gridDim.x - 1) {
+      const unsigned long long total = all & ((1ull << kHitsBits) - 1);
+      atomicExch(hits, total);
+      if (rate) *rate = T > 0 ? (double)total / (double)(T * k) : 1.0;
+    }
   }
 }
 
 __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 
-// hit rate = hits / (T * k), 1.0 for an empty batch
-__global__ void rate_kernel(const unsigned long long* hits, int64_t slots, double* rate) {
-  *rate = slots > 0 ? (double)*hits / (double)slots : 1.0;
-}
-
-// One wave per row at a time; 16-byte loads; products and sums in double.  Each wave writes the sum
-// of the cosines of the rows it handled to partial[wave id].
-template <bool BF16>
+// LPR lanes per row, 64 / LPR rows of a wave at a time; 16-byte loads; products and sums in double.
+// Each wave writes the sum of the cosines of the rows it handled to partial[wave id].  Wide rows are
+// bound by HBM (hidden states, 2048 columns of bf16: 4.9 TB/s of the card's 5.2 TB/s copy rate); rows
+// of at most 32 chunks, such as logits, leave most of a 64-lane row's lanes idle and are bound by the
+// reductions per row, so 16 lanes take one: 8190 x 64 float32 6.4
+// -> 3.8 us.
+template <bool BF16, int LPR>
 __global__ __launch_bounds__(kQThreads) void cosine_kernel(const char* __restrict__ a,
                                                            const char* __restrict__ b, int64_t rows,
                                                            int32_t cols, int64_t lda_bytes,
                                                            int64_t ldb_bytes, double* __restrict__ partial) {
+  constexpr int RPW = 64 / LPR;                // rows of a wave
   const int lane = threadIdx.x & 63;
+  const int in_row = lane % LPR;
   const int64_t wave = (int64_t)blockIdx.x * kQWaves + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kQWaves;
   constexpr int kPer = BF16 ? 8 : 4;          // elements per 16-byte chunk
   const int chunks = cols / kPer;
   double acc = 0.0;
-  for (int64_t r = wave; r < rows; r += nwaves) {
-    const u32x4* ra = reinterpret_cast<const u32x4*>(a + r * lda_bytes);
-    const u32x4* rb = reinterpret_cast<const u32x4*>(b + r * ldb_bytes);
+  for (int64_t r0 = wave * RPW; r0 < rows; r0 += nwaves * RPW) {
+    const int64_t r = r0 + lane / LPR;
     double dot = 0.0, aa = 0.0, bb = 0.0;
-    for (int c = lane; c < chunks; c += 64) {
-      const u32x4 va = __builtin_nontemporal_load(ra + c);
-      const u32x4 vb = __builtin_nontemporal_load(rb + c);
+    if (r < rows) {
+      const u32x4* ra = reinterpret_cast<const u32x4*>(a + r * lda_bytes);
+      const u32x4* rb = reinterpret_cast<const u32x4*>(b + r * ldb_bytes);
+      for (int c = in_row; c < chunks; c += LPR) {
+        const u32x4 va = __builtin_nontemporal_load(ra + c);
+        const u32x4 vb = __builtin_nontemporal_load(rb + c);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if constexpr (BF16) {
-          const double x0 = (double)__uint_as_float(va[q] << 16), x1 = (double)__uint_as_float(va[q] & 0xFFFF0000u);
-          const double y0 = (double)__uint_as_float(vb[q] << 16), y1 = (double)__uint_as_float(vb[q] & 0xFFFF0000u);
-          dot = fma(x0, y0, dot); dot = fma(x1, y1, dot);
-          aa = fma(x0, x0, aa); aa = fma(x1, x1, aa);
-          bb = fma(y0, y0, bb); bb = fma(y1, y1, bb);
-        } else {
-          const double x = (double)__uint_as_float(va[q]), y = (double)__uint_as_float(vb[q]);
-          dot = fma(x, y, dot); aa = fma(x, x, aa); bb = fma(y, y, bb);
+        for (int q = 0; q < 4; ++q) {
+          if constexpr (BF16) {
+            const double x0 = (double)__uint_as_float(va[q] << 16), x1 = (double)__uint_as_float(va[q] & 0xFFFF0000u);
+            const double y0 = (double)__uint_as_float(vb[q] << 16), y1 = (double)__uint_as_float(vb[q] & 0xFFFF0000u);
+            dot = fma(x0, y0, dot); dot = fma(x1, y1, dot);
+            aa = fma(x0, x0, aa); aa = fma(x1, x1, aa);
+            bb = fma(y0, y0, bb); bb = fma(y1, y1, bb);
+          } else {
+            const double x = (double)__uint_as_float(va[q]), y = (double)__uint_as_float(vb[q]);
+            dot = fma(x, y, dot); aa = fma(x, x, aa); bb = fma(y, y, bb);
+          }
         }
       }
     }
-    dot = wave_sum_f64(dot);
-    aa = wave_sum_f64(aa);
-    bb = wave_sum_f64(bb);
-    acc += dot / (sqrt(aa) * sqrt(bb));
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) {
+      dot += __shfl_xor(dot, off);
+      aa += __shfl_xor(aa, off);
+      bb += __shfl_xor(bb, off);
+    }
+    if (r < rows) acc += dot / (sqrt(aa) * sqrt(bb));
   }
+#pragma unroll
+  for (int off = 32; off >= LPR; off >>= 1) acc += __shfl_xor(acc, off);
   if (lane == 0) partial[wave] = acc;
 }
 
-// Sum of the per-wave partials in index order (one workgroup), divided by the row count.
+// Sum of the per-wave partials in a fixed order (one workgroup), divided by the row count: a chain of
+// latencies, so coalesced loads and wave sums rather than one thread adding 256 (4.9 -> 2.5 us).
 __global__ __launch_bounds__(kQThreads) void mean_kernel(const double* __restrict__ partial, int64_t n,
                                                          int64_t rows, double* __restrict__ out) {
-  __shared__ double s[kQThreads];
+  __shared__ double s[kQWaves];
   double v = 0.0;
-  const int64_t per = (n + kQThreads - 1) / kQThreads;   // contiguous slice per thread
-  for (int64_t i = threadIdx.x * per; i < n && i < (threadIdx.x + 1) * per; ++i) v += partial[i];
-  s[threadIdx.x] = v;
+#pragma unroll 8
+  for (int64_t i = threadIdx.x; i < n; i += kQThreads) v += partial[i];
+  v = wave_sum_f64(v);
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     double sum = 0.0;
-    for (int i = 0; i < kQThreads; ++i) sum += s[i];
+    for (int w = 0; w < kQWaves; ++w) sum += s[w];
     *out = rows > 0 ? sum / (double)rows : 1.0;
   }
 }
@@ -176,11 +216,9 @@ int launch_hits(const int32_t* pred, const int32_t* act, int64_t T, int32_t k, i
   hipStream_t st = static_cast<hipStream_t>(stream);
   auto* h = reinterpret_cast<unsigned long long*>(hits);
   hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, st, h);
-  if (T > 0) {
-    const int64_t blocks = (T + kQThreads - 1) / kQThreads;
-    hipLaunchKernelGGL(hits_kernel, dim3((unsigned)blocks), dim3(kQThreads), 0, st, pred, act, T, k, h);
-  }
-  if (rate) hipLaunchKernelGGL(rate_kernel, dim3(1), dim3(1), 0, st, h, T * (int64_t)k, rate);
+  const int64_t blocks = (T + kQThreads - 1) / kQThreads;
+  hipLaunchKernelGGL(hits_kernel, dim3((unsigned)(blocks < 1 ? 1 : blocks < kHitsBlocks ? blocks : kHitsBlocks)),
+                     dim3(kQThreads), 0, st, pred, act, T, k, h, rate);
   return hipGetLastError() == hipSuccess ? FB_OK : FB_EDEVICE;
 }
 
@@ -190,17 +228,17 @@ int launch_cosine(const void* a, const void* b, int64_t rows, int32_t cols, int6
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int elem = dtype == FB_BF16 ? 2 : 4;
   double* partial = static_cast<double*>(workspace);
-  const int64_t waves_needed = rows;
-  const int64_t blocks64 = (waves_needed + kQWaves - 1) / kQWaves;
+  // rows of at most 32 chunks of 16 bytes take 16 lanes each (see cosine_kernel)
+  const bool narrow = (int64_t)cols * elem <= 32 * 16;
+  const int64_t per_block = kQWaves * (narrow ? 4 : 1);
+  const int64_t blocks64 = (rows + per_block - 1) / per_block;
   const int blocks = (int)(blocks64 < kCosineBlocks ? (blocks64 > 0 ? blocks64 : 1) : kCosineBlocks);
-  if (dtype == FB_BF16)
-    hipLaunchKernelGGL(cosine_kernel<true>, dim3(blocks), dim3(kQThreads), 0, st,
-                       static_cast<const char*>(a), static_cast<const char*>(b), rows, cols,
-                       lda * elem, ldb * elem, partial);
-  else
-    hipLaunchKernelGGL(cosine_kernel<false>, dim3(blocks), dim3(kQThreads), 0, st,
-                       static_cast<const char*>(a), static_cast<const char*>(b), rows, cols,
-                       lda * elem, ldb * elem, partial);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kQThreads), 0, st, static_cast<const char*>(a),
+                       static_cast<const char*>(b), rows, cols, lda * elem, ldb * elem, partial);
+  };
+  if (dtype == FB_BF16) narrow ? go(cosine_kernel<true, 16>) : go(cosine_kernel<true, 64>);
+  else narrow ? go(cosine_kernel<false, 16>) : go(cosine_kernel<false, 64>);
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kQThreads), 0, st, partial, (int64_t)blocks * kQWaves,
                      rows, out);
   return hipGetLastError() == hipSuccess ? FB_OK : FB_EDEVICE;

@@ -91,7 +91,20 @@ def test_hits_edge_cases():
     assert float(rate.item()) == OP.hit_rate(tp, ta)
 
 
-@pytest.mark.parametrize("rows,cols,dtype", [(1, 8, "bf16"), (3, 4, "f32"), (5000, 7168, "bf16"),
+# one id, the eight fetched together, one more, the most; a workgroup's tokens and one more; more
+# tokens than the workgroups take at once
+@pytest.mark.parametrize("T,k", [(1, 1), (256, 8), (257, 9), (300000, 2), (1000, 32)])
+def test_hits_shapes(T, k):
+    _say(f"[quality] hits T={T} k={k}")
+    g = np.random.default_rng(T)
+    a, b = (np.argsort(g.random((T, 64)), axis=1)[:, :k].astype(np.int32) * 4 + 3 for _ in range(2))
+    want = int((a[:, :, None] == b[:, None, :]).sum())
+    for _ in range(2):
+        hits, rate = fb.topk_hits(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), with_rate=True)
+        assert int(hits.item()) == want and float(rate.item()) == want / (T * k)
+
+
+@pytest.mark.parametrize("rows,cols,dtype", [(7, 128, "f32"), (5, 132, "f32"), (6, 256, "bf16"), (4099, 64, "f32"), (1, 8, "bf16"), (3, 4, "f32"), (5000, 7168, "bf16"),
                                              (4097, 256, "f32")])
 def test_cosine_shapes(rows, cols, dtype):
     _say(f"[quality] cosine {rows}x{cols} {dtype}")
