@@ -509,6 +509,31 @@ def test_tiles_past_a_whole_round(T, H, dtype):
         assert np.array_equal(a["counts"], one["counts"])
 
 
+@pytest.mark.parametrize("E,k,offset", [(130, 9, 0), (256, 32, 1), (64, 6, 3), (40, 5, 0)])
+def test_debug_output_layouts(E, k, offset):
+    """Logits whose rows or base are not 16-byte aligned, and selections of more entries than lanes
+    per token, with many tied scores (ordered by expert)."""
+    _say(f"[outputs] E={E} k={k} offset={offset}")
+    T, H = 70, 64
+    g = np.random.default_rng(E)
+    x = g.integers(-1, 2, (T, H)).astype(np.float32)
+    w = (g.integers(-1, 2, (E, H)) * (g.random((E, H)) < 0.1)).astype(np.float32)
+    dev = torch.device("cuda", torch.cuda.current_device())
+    base = torch.full((T * E + 8,), 7.0, device=dev)
+    out = fb.Prediction(torch.empty(E, dtype=torch.int32, device=dev), torch.empty(1, dtype=torch.int32, device=dev),
+                        torch.empty(1, dtype=torch.float64, device=dev),
+                        torch.empty((T, k), dtype=torch.int32, device=dev), base[offset:offset + T * E].view(T, E))
+    fb.Predictor().predict_load(to_device(x, "f32"), to_device(w, "f32"), fb.Scoring("softmax", k),
+                                torch.zeros(E, dtype=torch.int32, device=dev), 1, out=out, return_topk=True,
+                                return_logits=True)
+    torch.cuda.synchronize()
+    z = x @ w.T                                     # whole numbers: exact in any order
+    assert np.array_equal(out.logits.cpu().numpy(), z)
+    assert np.array_equal(out.topk.cpu().numpy(), np.argsort(-z, axis=1, kind="stable")[:, :k])
+    rest = base.cpu().numpy()
+    assert (rest[:offset] == 7.0).all() and (rest[offset + T * E:] == 7.0).all()
+
+
 def test_qwen3_layers_back_to_back():
     """Qwen3-MoE-shaped layers (every token against the oracle) and the device plan of each layer's
     counts under the config's budget against the oracle's plan.  All 48 layers run in bench.py's
