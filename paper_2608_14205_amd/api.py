@@ -616,21 +616,40 @@ def _cosine_workspace(device: torch.device) -> torch.Tensor:
     return ws
 
 
-def row_cosine_mean(a: torch.Tensor, b: torch.Tensor,
-                    stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
-    """fb_row_cosine_mean: mean over rows of cos(a[r], b[r]) as a device float64 scalar."""
+def _row_cosine_into(out: torch.Tensor, a: torch.Tensor, b: torch.Tensor,
+                     stream: Optional[torch.cuda.Stream]) -> None:
     if a.dim() != 2 or a.shape != b.shape or a.dtype != b.dtype or a.device != b.device:
         raise ValueError("a and b must be matching 2-D tensors on one device")
     if a.stride(1) != 1 or b.stride(1) != 1:
         raise ValueError("rows must be contiguous")
-    _one_gpu(a.device, a, b)
-    out = torch.empty(1, dtype=torch.float64, device=a.device)
+    _one_gpu(a.device, a, b, out)
     ws = _cosine_workspace(a.device)
     with torch.cuda.device(a.device):
         L.check(L.lib().fb_row_cosine_mean(_ptr(a), _ptr(b), a.shape[0], a.shape[1], a.stride(0),
                                            b.stride(0), _dtype_code(a), _ptr(out), _ptr(ws), ws.numel(),
                                            _stream_handle(a.device, stream)), "fb_row_cosine_mean")
+
+
+def row_cosine_mean(a: torch.Tensor, b: torch.Tensor,
+                    stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
+    """fb_row_cosine_mean: mean over rows of cos(a[r], b[r]) as a device float64 scalar."""
+    out = torch.empty(1, dtype=torch.float64, device=a.device)
+    _row_cosine_into(out, a, b, stream)
     return out
+
+
+def _topk_hits_into(out: torch.Tensor, rate: Optional[torch.Tensor], topk_pred: torch.Tensor,
+                    topk_actual: torch.Tensor, stream: Optional[torch.cuda.Stream]) -> None:
+    if topk_pred.shape != topk_actual.shape or topk_pred.dim() != 2:
+        raise ValueError("top-k tables must both be T x k")
+    for t in (topk_pred, topk_actual):
+        if t.dtype != torch.int32 or not t.is_contiguous():
+            raise ValueError("top-k tables must be contiguous int32")
+    _one_gpu(topk_pred.device, topk_pred, topk_actual, out, rate)
+    with torch.cuda.device(topk_pred.device):
+        L.check(L.lib().fb_topk_hits(_ptr(topk_pred), _ptr(topk_actual), topk_pred.shape[0],
+                                     topk_pred.shape[1], _ptr(out), _ptr(rate),
+                                     _stream_handle(topk_pred.device, stream)), "fb_topk_hits")
 
 
 def topk_hits(topk_pred: torch.Tensor, topk_actual: torch.Tensor,
@@ -638,18 +657,9 @@ def topk_hits(topk_pred: torch.Tensor, topk_actual: torch.Tensor,
               with_rate: bool = False):
     """fb_topk_hits: sum over tokens of the predicted and actual sets' intersection size (device
     int64); with_rate=True also returns the device-computed hit rate hits / (T k) (float64)."""
-    if topk_pred.shape != topk_actual.shape or topk_pred.dim() != 2:
-        raise ValueError("top-k tables must both be T x k")
-    for t in (topk_pred, topk_actual):
-        if t.dtype != torch.int32 or not t.is_contiguous():
-            raise ValueError("top-k tables must be contiguous int32")
-    _one_gpu(topk_pred.device, topk_pred, topk_actual)
     out = torch.empty(1, dtype=torch.int64, device=topk_pred.device)
     rate = torch.empty(1, dtype=torch.float64, device=topk_pred.device) if with_rate else None
-    with torch.cuda.device(topk_pred.device):
-        L.check(L.lib().fb_topk_hits(_ptr(topk_pred), _ptr(topk_actual), topk_pred.shape[0],
-                                     topk_pred.shape[1], _ptr(out), _ptr(rate),
-                                     _stream_handle(topk_pred.device, stream)), "fb_topk_hits")
+    _topk_hits_into(out, rate, topk_pred, topk_actual, stream)
     return (out, rate) if with_rate else out
 
 
@@ -700,8 +710,22 @@ def prediction_quality(pred: Prediction, actual: Prediction, hidden_prev: Option
     carry topk (and logits for the logit cosine)."""
     if pred.topk is None or actual.topk is None:
         raise ValueError("both passes need return_topk=True")
-    hits, rate = topk_hits(pred.topk, actual.topk, with_rate=True)
-    lc = row_cosine_mean(pred.logits, actual.logits) if pred.logits is not None and actual.logits is not None else None
-    hc = row_cosine_mean(hidden_prev, hidden_target) if hidden_prev is not None and hidden_target is not None else None
-    return Quality(int(hits.item()), float(rate.item()), None if lc is None else float(lc.item()),
-                   None if hc is None else float(hc.item()))
+    # the results share one buffer, read back once: a read-back per value waited for the GPU four
+    # times (a 64-expert study of 8190 tokens: 137 -> 102 us)
+    res = torch.empty(4, dtype=torch.int64, device=pred.topk.device)
+    real = res.view(torch.float64)
+    _topk_hits_into(res[0:1], real[1:2], pred.topk, actual.topk, None)
+    pairs = [(pred.logits, actual.logits), (hidden_prev, hidden_target)]
+    apart = [None, None]
+    for i, (a, b) in enumerate(pairs):
+        if a is None or b is None:
+            continue
+        if a.device == res.device:
+            _row_cosine_into(real[2 + i:3 + i], a, b, None)
+        else:                                    # on another GPU than the selections
+            apart[i] = float(row_cosine_mean(a, b).item())
+    got = res.cpu()
+    rates = got.view(torch.float64).tolist()
+    cosines = [None if a is None or b is None else apart[i] if apart[i] is not None else rates[2 + i]
+               for i, (a, b) in enumerate(pairs)]
+    return Quality(int(got[0]), rates[1], cosines[0], cosines[1])
