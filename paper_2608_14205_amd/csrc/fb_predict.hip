@@ -529,12 +529,17 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
       bi = bn;
     }
   }
+  // no stage load may still be writing LDS when the tile is reused below, and the fragments fetched past
+  // the last stage keep their registers until they have landed
+  __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+#pragma unroll
+  for (int i = 0; i < kRingW; ++i) pin_acc(ring[i]);
+  pin(bq[0]);
+  pin(bq[1]);
   if constexpr (!BF16) {                         // the last pair of k-steps
     mma_parts(sa[1], sb[1], 0);
     mma_parts(sa[1], sb[1], 1);
   }
-  // no stage load may still be writing LDS when the tile is reused below
-  __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
 }
 
 // Score of one logit without its bias lb (LBIAS: add it; padding experts hold -inf there and in sb).
