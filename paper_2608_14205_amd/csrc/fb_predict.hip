@@ -1002,6 +1002,10 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
     // which is a chain of LDS reads, k steps of about 0.1 us.  With the
     // logits in 16-byte stores: E = 256, T = 16384, k = 8 92.5 -> 82.5 us with both outputs, E = 128, T
     // = 16000 31.2 -> 28.0.
+    // Counting places every entry once only if the scores are ordered: a NaN compares false with every
+    // score and would leave slots unwritten, so a token whose entries hold one is sorted by insertion,
+    // which permutes whatever it is given.  Every lane that counts sees all k scores.
+    bool ordered = G > 1;
     if (p.topk_idx && G > 1 && tv) {
       const int16_t* list = sel[tlu];
       for (int r = jg; r < k; r += G) {
@@ -1013,11 +1017,12 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
           const int eo = list[q];
           const float so = (unsigned)eo < (unsigned)E ? S[tlu * SROW + eo] : -__builtin_inff();
           rank += (int)(so > se) | ((int)(so == se) & (int)(eo < e));
+          ordered &= so == so;
         }
-        p.topk_idx[ttu * k + rank] = e;
+        if (ordered) p.topk_idx[ttu * k + rank] = e;
       }
     }
-    if (p.topk_idx && G == 1 && tv) {
+    if (p.topk_idx && !ordered && jg == 0 && tv) {
       int16_t* list = sel[tlu];
       for (int r = 1; r < k; ++r) {
         const int e = list[r];

@@ -534,6 +534,41 @@ def test_debug_output_layouts(E, k, offset):
     assert (rest[:offset] == 7.0).all() and (rest[offset + T * E:] == 7.0).all()
 
 
+@pytest.mark.parametrize("E,k,H,dtype,kind", [(16, 4, 64, "bf16", "softmax"), (64, 6, 64, "bf16", "sigmoid"),
+                                              (128, 8, 64, "f32", "softmax"), (130, 9, 64, "f32", "softmax"),
+                                              (256, 8, 64, "bf16", "sigmoid"), (256, 32, 4096, "bf16", "softmax")])
+def test_nan_scores_still_fill_the_selections(E, k, H, dtype, kind):
+    """A token with NaN scores (a NaN hidden value: all of them; a NaN weight row: one expert's, in
+    every token) still gets k distinct experts written, the ones counted; other tokens are not
+    affected.  Fused, and with H = 4096 split launches."""
+    _say(f"[nan] E={E} k={k} H={H} {dtype} {kind}")
+    T = 70
+    g = np.random.default_rng(E + k)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.from_numpy(g.integers(-1, 2, (T, H)).astype(np.float32))
+    w = torch.from_numpy((g.integers(-1, 2, (E, H)) * (g.random((E, H)) < 0.1)).astype(np.float32))
+    x[5, 3] = x[69, 0] = float("nan")
+    w_nan = w.clone()
+    w_nan[2, 1] = float("nan")
+    for weight, nan_rows in ((w, [5, 69]), (w_nan, range(T))):
+        out = fb.Prediction(torch.empty(E, dtype=torch.int32, device="cuda"),
+                            torch.empty(1, dtype=torch.int32, device="cuda"),
+                            torch.empty(1, dtype=torch.float64, device="cuda"),
+                            torch.full((T, k), -7, dtype=torch.int32, device="cuda"))
+        fb.Predictor().predict_load(x.to(dt).cuda(), fb.pack_router_weight(weight.to(dt).cuda()),
+                                    fb.Scoring(kind, k), torch.zeros(E, dtype=torch.int32, device="cuda"), 1,
+                                    out=out, return_topk=True)
+        torch.cuda.synchronize()
+        topk = out.topk.cpu().numpy()
+        assert topk.min() >= 0 and topk.max() < E
+        assert (np.diff(np.sort(topk, axis=1), axis=1) > 0).all()
+        assert np.array_equal(out.counts.cpu().numpy(), np.bincount(topk.ravel(), minlength=E))
+        rows = np.setdiff1d(np.arange(T), list(nan_rows))
+        if rows.size and kind == "softmax":
+            z = (x @ w.T).numpy()[rows]              # whole numbers: exact in any order
+            assert np.array_equal(topk[rows], np.argsort(-z, axis=1, kind="stable")[:, :k])
+
+
 def test_qwen3_layers_back_to_back():
     """Qwen3-MoE-shaped layers (every token against the oracle) and the device plan of each layer's
     counts under the config's budget against the oracle's plan.  All 48 layers run in bench.py's
