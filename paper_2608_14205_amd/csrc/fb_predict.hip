@@ -19,7 +19,8 @@
 //     L2-resident) straight into registers through a ring of 16 k-step slices, 15 k-steps ahead of
 //     the MFMAs; the hidden fragments are read from LDS one k-step ahead.  The router weight is the
 //     A operand (M = experts) and the hidden tile is B (N = tokens): v_mfma_f32_32x32x16_bf16 (or
-//     the same on split values for f32), so each lane ends with groups of four consecutive experts of one token.
+//     v_mfma_f32_32x32x2_f32, or bf16 parts of the values, for f32), so each lane ends with groups of four
+//     consecutive experts of one token.
 //   * One workgroup barrier per stage, placed before the stage's last k-step: it publishes the next
 //     stage (every wave waits for its own share of that stage's loads first) and frees the buffer
 //     just read, which the next load batch then refills.  Waits are counted, never drained.
@@ -292,10 +293,14 @@ __global__ void pack_kernel(const char* __restrict__ w, int32_t E, int32_t Hbyte
 
 // ---- the contraction ---------------------------------------------------------------------------
 // acc[fe][ft] += (router weight block fe) x (hidden block ft) over every stage of the tile; the NS
-// stage buffers start at ring_lds.
-template <bool BF16, int EPAD, int FE, int FT, int NS, int BM, int TW>
+// stage buffers start at ring_lds.  MATH: bf16 inputs, float32 inputs in bf16 parts, or float32 inputs
+// on the float32 matrix instructions.  kParts: *odd gets a non-zero lower half when some value is not
+// the sum of its parts.
+constexpr int kBf16 = 0, kParts = 1, kExact = 2;
+template <int MATH, int EPAD, int FE, int FT, int NS, int BM, int TW>
 __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p, int64_t row0,
-                                         int wave, int we, int wt, int lane, char* ring_lds) {
+                                         int wave, int we, int wt, int lane, char* ring_lds,
+                                         uint32_t* odd) {
   constexpr int LPW = BM / 4 / kWaves;               // stage load instructions per wave (4 rows each)
   constexpr int UNROLL = kRingW / kNStep;            // one period of the weight ring per iteration
   constexpr int STAGE = BM * kStageRowBytes;         // LDS bytes of one stage buffer
@@ -400,25 +405,39 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-      for (int fe = 0; fe < FE; ++fe)
-        acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            __builtin_bit_cast(bf16x8, a[fe]), __builtin_bit_cast(bf16x8, b[ft]), acc[fe][ft], 0, 0, 0);
+      for (int fe = 0; fe < FE; ++fe) {
+        if constexpr (MATH == kBf16) {
+          acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8, a[fe]), __builtin_bit_cast(bf16x8, b[ft]), acc[fe][ft], 0, 0, 0);
+        } else {
+          // four k-pairs per fragment; A and B take the same k for every lane
+          const f32x4 av = __builtin_bit_cast(f32x4, a[fe]);
+          const f32x4 bv = __builtin_bit_cast(f32x4, b[ft]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc[fe][ft], 0, 0, 0);
+        }
+      }
   };
-  // float32 inputs: every value is the exact sum of three bf16 parts (its upper 16 bits, which no value
-  // overflows; the rest rounded to bf16, so that what is left has either sign; what is left, whose 8
-  // bits fit), and the product keeps the six part products above 2^-22 of it, on bf16 MFMAs with
-  // float32 accumulation.  Two k-steps (8 values of a lane) make one
-  // fragment; the MFMAs of a pair of k-steps run among the splitting of the next pair, half of them
-  // per k-step, so the vector ALU works beside the matrix cores.  Bound by the two in balance (E =
-  // 256: 96 vector and 12 matrix instructions per k-step and wave, 64 rows); the six products need
-  // 0.38 of the matrix time of v_mfma_f32_32x32x2_f32, which this replaced: E = 256, H = 7168, T =
-  // 20000 865 -> 450 us, T = 4096 with selections and logits written 143 -> 102, E = 64, H = 2048, T =
-  // 1000 25.4 -> 20.7.  The logits' error against 64 bits is smaller (fewer accumulations): 1.49e-6
-  // -> 1.35e-6 and 3.9e-7 -> 3.0e-7 of their norm at those two widths.
+  // float32 inputs in parts: every value is the sum of three bf16 parts (the value rounded to bf16, the
+  // rest rounded to bf16, what is left), and the product keeps six of the nine part products, on bf16
+  // MFMAs with float32 accumulation: the three left out are below 2^-24 of it.  Two k-steps (8 values of
+  // a lane) make one fragment; the MFMAs of a pair of k-steps run among the splitting of the next pair,
+  // half of them per k-step, so the vector ALU works beside the matrix cores.  The sum is exact unless a
+  // value is too large to be rounded to bf16 or so small (below 2^-109) that what is left reaches past
+  // bf16's exponents; `left` gathers the bits that the last part leaves out.
+  // Bound by vector and matrix instructions in balance (E = 256: 104 and 12 per k-step and wave, 64
+  // rows); the six products need 0.38 of the matrix time of v_mfma_f32_32x32x2_f32.  Where the parts
+  // serve (see parts_pay), the error against 64 bits on dense rows is smaller (fewer accumulations):
+  // 2.4e-7 instead of 2.9e-7 of the logits' norm at H = 512.  On rows with a single non-zero value it is
+  // 3.5e-8 instead of 2.5e-8: the bf16 MFMA truncates as it accumulates, and keeping eight products
+  // (3.45e-8) would cost 10 to 20% more time.
   struct Parts { u32x4 v[3]; };
-  constexpr int kSplitOps = (FE + FT) * 22 + FE * 4;   // vector instructions of a k-step's splitting
+  constexpr int kProducts = 6;
+  constexpr int kSplitOps = (FE + FT) * 24 + FE * 4;   // vector instructions of a k-step's splitting
   Parts sa[2][FE], sb[2][FT];                    // [parity of the k-step pair]
-  if constexpr (!BF16) {
+  uint32_t left = 0;                             // bits of every value that its parts leave out
+  if constexpr (MATH == kParts) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
 #pragma unroll
@@ -431,28 +450,30 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   auto split4 = [&](Parts& out, const u32x4& x, int half) {
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
-      const uint32_t a = x[2 * w], b = x[2 * w + 1];
-      const float ra = __uint_as_float(a) - __uint_as_float(a & 0xFFFF0000u);
-      const float rb = __uint_as_float(b) - __uint_as_float(b & 0xFFFF0000u);
+      const float a = __uint_as_float(x[2 * w]), b = __uint_as_float(x[2 * w + 1]);
+      const uint32_t h = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+      const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
       const uint32_t m = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
-      const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
-      out.v[0][2 * half + w] = __builtin_amdgcn_perm(b, a, 0x07060302u);       // upper halves
+      const uint32_t la = __float_as_uint(ra - __uint_as_float(m << 16));
+      const uint32_t lb = __float_as_uint(rb - __uint_as_float(m & 0xFFFF0000u));
+      out.v[0][2 * half + w] = h;
       out.v[1][2 * half + w] = m;
-      out.v[2][2 * half + w] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
+      out.v[2][2 * half + w] = __builtin_amdgcn_perm(lb, la, 0x07060302u);   // upper halves
+      left = left | la | lb;
     }
   };
-  // three of the six part products of a pair of k-steps, smallest parts first
+  // half of the part products of a pair of k-steps, smallest parts first
   auto mma_parts = [&](const Parts(&a)[FE], const Parts(&b)[FT], int half) {
-    constexpr int kI[6] = {2, 0, 1, 1, 0, 0}, kJ[6] = {0, 2, 1, 0, 1, 0};
+    constexpr int kI[kProducts] = {2, 0, 1, 1, 0, 0}, kJ[kProducts] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < kProducts / 2; ++i)
 #pragma unroll
       for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
         for (int fe = 0; fe < FE; ++fe)
           acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8, a[fe].v[kI[3 * half + i]]),
-              __builtin_bit_cast(bf16x8, b[ft].v[kJ[3 * half + i]]), acc[fe][ft], 0, 0, 0);
+              __builtin_bit_cast(bf16x8, a[fe].v[kI[kProducts / 2 * half + i]]),
+              __builtin_bit_cast(bf16x8, b[ft].v[kJ[kProducts / 2 * half + i]]), acc[fe][ft], 0, 0, 0);
   };
 
   // ---- prologue: stages 0 .. NS-1 and k-steps 0 .. kRingW-2 in flight, then stage 0 published.
@@ -508,7 +529,7 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
         wait_w(q);                              // this k-step's weight slice
         pin(bq[q & 1]);
         pin_acc(ring[slot]);
-        if constexpr (BF16) {
+        if constexpr (MATH != kParts) {
           mma(ring[slot], bq[q & 1]);
         } else {
           const int par = (q >> 1) & 1;
@@ -518,11 +539,13 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
           for (int ft = 0; ft < FT; ++ft) split4(sb[par][ft], bq[q & 1][ft], q & 1);
           mma_parts(sa[par ^ 1], sb[par ^ 1], q & 1);
 #pragma unroll
-          for (int i = 0; i < 3 * FE * FT; ++i) {
+          for (int i = 0; i < kProducts / 2 * FE * FT; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, kSplitOps / (3 * FE * FT), 0);   // its vector share
+            __builtin_amdgcn_sched_group_barrier(0x002, kSplitOps / (kProducts / 2 * FE * FT), 0);   // its vector share
           }
         }
+        // the bits left out are gathered in the k-step they come from, not kept apart until the end
+        if constexpr (MATH == kParts) asm volatile("" : "+v"(left));
         // keep every load in the k-step it was written in: the prefetch distances are the design
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -536,9 +559,10 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   for (int i = 0; i < kRingW; ++i) pin_acc(ring[i]);
   pin(bq[0]);
   pin(bq[1]);
-  if constexpr (!BF16) {                         // the last pair of k-steps
+  if constexpr (MATH == kParts) {                // the last pair of k-steps
     mma_parts(sa[1], sb[1], 0);
     mma_parts(sa[1], sb[1], 1);
+    *odd = left;
   }
 }
 
@@ -571,6 +595,18 @@ constexpr int kArrivalPolls = 256;
 // Arrival word of a tile: arrivals in the low half, given-up slices (one bit per split) in the high.
 constexpr uint32_t kArrivalMask = 0xFFFFu;
 static_assert(kMaxSplits <= 16, "one given-up bit per split in the arrival word");
+
+// Whether float32 inputs are contracted in parts.  Float32 matrix instructions / parts (us per packed
+// call): E = 8, H = 4096, T = 1000 20.9 / 21.9; E = 64, H = 2048, T = 1000 19.6 / 20.4, T = 30000 96.0 /
+// 104.8; E = 128, H = 2048, T = 1000 27.2 / 26.0, T = 20000 150.5 / 132.2; E = 256, H = 7168, T = 64
+// 43.7 / 35.1, T = 4096 with selections and logits 133 / 105, T = 20000 866 / 463.
+constexpr bool parts_pay(int epad) { return epad >= 128; }
+// The parts serve a workgroup whose values are all sums of their parts and whose logits are zero or at
+// least 2^-100 (below, part products would underflow that a float32 product keeps) and finite.  Any
+// other workgroup (infinities and values next to the largest among them, as both parts of such a value
+// are infinite or NaN) contracts again on the float32 matrix instructions and has their results.
+// kLeastLogit: 2^-100, doubled, as bits, less one.
+constexpr uint32_t kLeastLogit = (27u << 24) - 1u;
 
 // BM_: tokens per workgroup (the configuration's own, or half of it when that fills the chip better)
 // MODE: kFused contracts the whole row and finishes the tile.  Split mode (grid tiles x ks) contracts
@@ -613,6 +649,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   __shared__ int32_t s_flag;
   __shared__ uint32_t s_marks;
   __shared__ int32_t s_stray;                     // an expert on a rank that does not exist
+  __shared__ int32_t s_redo;                      // float32: the parts do not serve this workgroup's values
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -650,8 +687,40 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
       q.st_base = split * chunk;
       q.nstages = p.st_total - q.st_base < chunk ? p.st_total - q.st_base : chunk;
     }
-    if (row0 < p.T && q.nstages > 0)
-      contract<BF16, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem);
+    const bool any = row0 < p.T && q.nstages > 0;
+    if constexpr (BF16 || !parts_pay(EPAD)) {
+      if (any)
+        contract<BF16 ? kBf16 : kExact, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem, nullptr);
+    } else {
+      if (tid == 0) s_redo = 0;
+      if (any) {
+        uint32_t odd = 0;
+        contract<kParts, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem, &odd);
+        odd &= 0xFFFFu;
+        uint32_t least = ~0u;                      // of 2 |logit| - 1 as bits: zeros do not count
+        float finite = 0.f;                        // NaN with any logit that is not
+#pragma unroll
+        for (int a = 0; a < FE; ++a)
+#pragma unroll
+          for (int b = 0; b < FT; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              least = min(least, (__float_as_uint(acc[a][b][r]) << 1) - 1u);
+              finite = fmaf(acc[a][b][r], 0.f, finite);
+            }
+        if (odd != 0 || least < kLeastLogit || finite != finite) s_redo = 1;
+        lds_barrier();
+        if (s_redo != 0) {
+#pragma unroll
+          for (int a = 0; a < FE; ++a)
+#pragma unroll
+            for (int b = 0; b < FT; ++b)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+          contract<kExact, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem, nullptr);
+        }
+      }
+    }
   }
   lds_barrier();
 

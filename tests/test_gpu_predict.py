@@ -462,9 +462,10 @@ def test_split_slices(E, T, H, dtype):
 @pytest.mark.parametrize("E,H,T,scale", [(16, 64, 40, 1.0), (200, 272, 130, 2.0 ** 60), (256, 1040, 70, 2.0 ** -60)])
 def test_f32_values(E, H, T, scale):
     """float32 logits of values with full mantissas, widely spread exponents and either sign against
-    float64.  Each value is exactly h + m + l with |m| <= 2^-7 |x| (the rest of truncating to 8 bits)
-    and |l| <= 2^-16 |x| (that rest rounded to 8 bits), so the products left out, m l', l m' and l l',
-    are below 2^-21.9 |x w|; the six kept are added in 6 H / 16 float32 accumulations."""
+    float64.  With more than 64 experts each value is exactly h + m + l with |m| <= 2^-8 |x| (the rest
+    of rounding to 8 bits) and |l| <= 2^-17 |x| (the rest of rounding that), so the products left out,
+    m l', l m' and l l', are below 2^-23.9 |x w|; the six kept are added in 6 H / 16 float32
+    accumulations.  With 64 experts or fewer nothing is left out and H / 2 are added."""
     _say(f"[f32] E={E} H={H} T={T} scale={scale}")
     g = np.random.default_rng(E)
     x = (g.standard_normal((T, H)) * np.exp2(g.integers(-12, 13, (T, H))) * scale).astype(np.float32)
@@ -478,9 +479,64 @@ def test_f32_values(E, H, T, scale):
     torch.cuda.synchronize()
     ref = x.astype(np.float64) @ w.astype(np.float64).T
     mag = np.abs(x).astype(np.float64) @ np.abs(w).astype(np.float64).T
-    bound = (2.0 ** -21.9 + (6 * H / 16 + 24) * 2.0 ** -24) * mag
+    bound = (2.0 ** -23.9 + (6 * H / 16 + 24) * 2.0 ** -24) * mag
     err = np.abs(out.logits.cpu().numpy() - ref)
     assert (err <= bound).all(), float((err / np.maximum(bound, 1e-300)).max())
+
+
+def _logits_f32(x, w):
+    out = fb.Predictor().predict_load(to_device(x, "f32"), fb.pack_router_weight(to_device(w, "f32")),
+                                      fb.Scoring("softmax", 2),
+                                      torch.zeros(len(w), dtype=torch.int32, device="cuda"), 1, return_logits=True)
+    torch.cuda.synchronize()
+    return out.logits.cpu().numpy()
+
+
+@pytest.mark.parametrize("E,H", [(16, 64), (100, 64), (256, 64), (256, 4096)])
+@pytest.mark.parametrize("sx,sw", [(-106, 60), (-112, 60), (-120, 60), (-130, 100), (-140, 120), (60, -115), (-61, -61)])
+def test_f32_small_values(E, H, sx, sw):
+    """float32 values near and below the smallest normal ones, which have no bits left for three bf16
+    parts, and products near the smallest float32: rows with a single value, so that nothing larger
+    hides what is lost, then dense rows.  A float32 contraction rounds once per two products; parts of
+    2^-106 are still exact and cost a product 2^-23.9 and two truncations of 2^-23 more.  The bound
+    allows as many roundings of 2^-24 and as many of half the smallest float32."""
+    _say(f"[f32 small] E={E} H={H} 2^{sx} 2^{sw}")
+    g = np.random.default_rng(E + H - sx)
+    T = 130                                          # the last tile's rows only are dense
+    x = np.zeros((T, H), np.float32)
+    x[np.arange(T), g.integers(0, H, T)] = 1 + g.random(T)
+    x[T - 2:] = g.standard_normal((2, H))
+    x = (x.astype(np.float64) * 2.0 ** sx).astype(np.float32)
+    w = (g.uniform(1, 2, (E, H)) * g.choice([-1.0, 1.0], (E, H)) * 2.0 ** sw).astype(np.float32)
+    got = _logits_f32(x, w)
+    ref = x.astype(np.float64) @ w.astype(np.float64).T
+    mag = np.abs(x).astype(np.float64) @ np.abs(w).astype(np.float64).T
+    terms = np.minimum((x != 0).sum(1) + 1, H / 2 + 1)[:, None] + 5
+    err = np.abs(got - ref)
+    assert (err <= terms * (2.0 ** -24 * mag + 2.0 ** -150)).all(), float((err / np.maximum(mag, 1e-300)).max())
+
+
+# fused; many splits; 128-row tiles past whole rounds: whole ones, then one in splits
+@pytest.mark.parametrize("E,H,T", [(16, 64, 200), (100, 64, 200), (256, 64, 200), (256, 4096, 200), (256, 528, 32868)])
+def test_f32_large_and_infinite_values(E, H, T):
+    """Infinite and NaN values and finite ones that no bf16 holds (above its largest) give the logits
+    float32 arithmetic gives; rows of other tiles are not affected."""
+    _say(f"[f32 large] E={E} H={H} T={T}")
+    g = np.random.default_rng(E + H)
+    x = g.integers(-2, 3, (T, H)).astype(np.float32)
+    w = (g.integers(1, 3, (E, H)) * g.choice([-1, 1], (E, H))).astype(np.float32)
+    x[3, 5], x[4, 7], x[5, 1], x[150, H - 1] = np.inf, -np.inf, np.nan, np.inf
+    x[T - 1, H - 1] = np.inf
+    x[6], x[7] = 0, 0
+    x[6, 2], x[7, 9] = 0.25 * np.float32(3.4e38), np.float32(3.4028235e38)
+    w[:, 9] = np.sign(w[:, 9])
+    for column in (None, 1):
+        if column is not None:
+            w[column, 3] = np.inf                    # one expert's weight: one column of logits
+        got = _logits_f32(x, w)
+        with np.errstate(invalid="ignore"):          # whole numbers and single values: exact in any order
+            ref = (x.astype(np.float64) @ w.astype(np.float64).T).astype(np.float32)
+        assert np.array_equal(got, ref, equal_nan=True)
 
 
 # one token past a whole round (16 splits), 65 tiles past it (two splits), a round and a half in f32
