@@ -1091,12 +1091,14 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
         if (ordered) p.topk_idx[ttu * k + rank] = e;
       }
     }
-    if (p.topk_idx && !ordered && jg == 0 && tv) {
+    if (p.topk_idx && (G == 1 || __builtin_expect(!ordered, 0)) && jg == 0 && tv) {
       int16_t* list = sel[tlu];
+#pragma unroll 1
       for (int r = 1; r < k; ++r) {
         const int e = list[r];
         const float se = (unsigned)e < (unsigned)E ? S[tlu * SROW + e] : -__builtin_inff();
         int q = r;
+#pragma unroll 1
         while (q > 0) {
           const int eo = list[q - 1];
           const float so = (unsigned)eo < (unsigned)E ? S[tlu * SROW + eo] : -__builtin_inff();
@@ -1106,6 +1108,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
         }
         list[q] = (int16_t)e;
       }
+#pragma unroll 1
       for (int r = 0; r < k; ++r) p.topk_idx[ttu * k + r] = list[r];
     }
   };
