@@ -199,6 +199,7 @@ fb::PredictLaunch make_launch(const void* hidden, int64_t T, int32_t H, int64_t 
   a.num_cus = fb::device_cu_count();
   a.partial = nullptr;
   a.partial_bytes = 0;
+  a.arrival_polls = fb::kArrivalPolls;
   a.plan = nullptr;
   return a;
 }
@@ -316,13 +317,13 @@ int fb_predict_load(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,
                                         max_mean, workspace, topk_idx, logits, stream));
 }
 
-int fb_predict_load_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,
-                           int32_t dtype, const void* router_packed, size_t router_packed_bytes,
-                           int32_t E, const float* logit_bias, const float* select_bias,
-                           const fb_scoring* scoring, const int32_t* expert_to_rank, int32_t R,
-                           int32_t* counts, int32_t* rank_loads, double* max_mean,
-                           void* workspace, size_t workspace_bytes, int32_t* topk_idx,
-                           float* logits, void* stream) {
+int fb_test_predict_load_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,
+                                int32_t dtype, const void* router_packed, size_t router_packed_bytes,
+                                int32_t E, const float* logit_bias, const float* select_bias,
+                                const fb_scoring* scoring, const int32_t* expert_to_rank, int32_t R,
+                                int32_t* counts, int32_t* rank_loads, double* max_mean, void* workspace,
+                                size_t workspace_bytes, int32_t* topk_idx, float* logits, void* stream,
+                                int32_t arrival_polls) {
   if (!router_packed) return FB_EINVAL;
   const int vc = check_predict(hidden, T, H, ld_hidden, dtype, E, select_bias, scoring,
                                expert_to_rank, R, counts, rank_loads, max_mean, workspace,
@@ -341,7 +342,21 @@ int fb_predict_load_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_
     a.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + fb::kWsBytes);
     a.partial_bytes = workspace_bytes - fb::kWsBytes;
   }
+  a.arrival_polls = arrival_polls;
   return fb::launch_predict(a);
+}
+
+int fb_predict_load_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,
+                           int32_t dtype, const void* router_packed, size_t router_packed_bytes,
+                           int32_t E, const float* logit_bias, const float* select_bias,
+                           const fb_scoring* scoring, const int32_t* expert_to_rank, int32_t R,
+                           int32_t* counts, int32_t* rank_loads, double* max_mean,
+                           void* workspace, size_t workspace_bytes, int32_t* topk_idx,
+                           float* logits, void* stream) {
+  return fb_test_predict_load_packed(hidden, T, H, ld_hidden, dtype, router_packed, router_packed_bytes, E,
+                                     logit_bias, select_bias, scoring, expert_to_rank, R, counts, rank_loads,
+                                     max_mean, workspace, workspace_bytes, topk_idx, logits, stream,
+                                     fb::kArrivalPolls);
 }
 
 int fb_predict_plan_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,

@@ -34,10 +34,15 @@ struct PredictLaunch {
   int32_t num_cus;    // compute units of the device (tile-height choice)
   float* partial;     // split mode: partial-logit buffer in the workspace, or NULL
   size_t partial_bytes;
+  int32_t arrival_polls;  // split mode: see kArrivalPolls
   // the swap plan of the counts, made in the predictor's last workgroup (frontier mode, R <= 64,
   // S * S <= 128; see plan_fusable), or NULL
   const PlanDeviceLaunch* plan;
 };
+// Polls of a tile's arrival word before a workgroup gives its slice to the tile's last arrival: each
+// is a trip to memory (0.2 us or more), so at least 50 us in all, several times the spread of one
+// launch's workgroups.
+constexpr int32_t kArrivalPolls = 256;
 // Bytes of partial logits the split mode needs for a batch (0: that batch runs fused).
 size_t split_workspace_bytes(int64_t T, int32_t E, int32_t H, int32_t dtype, int num_cus);
 
@@ -117,3 +122,14 @@ int check_device();
 int device_cu_count();
 
 }  // namespace fb
+
+// fb_predict_load_packed with another number of polls (0: every workgroup that is not its tile's last
+// gives its slice up), so that tests reach what an idle GPU does not.  Not part of the interface.
+extern "C" int fb_test_predict_load_packed(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden,
+                                           int32_t dtype, const void* router_packed,
+                                           size_t router_packed_bytes, int32_t E, const float* logit_bias,
+                                           const float* select_bias, const fb_scoring* scoring,
+                                           const int32_t* expert_to_rank, int32_t R, int32_t* counts,
+                                           int32_t* rank_loads, double* max_mean, void* workspace,
+                                           size_t workspace_bytes, int32_t* topk_idx, float* logits,
+                                           void* stream, int32_t arrival_polls);

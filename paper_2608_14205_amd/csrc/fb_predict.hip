@@ -107,6 +107,7 @@ struct Params {
   int32_t ks;          // splits of the stage range (split mode); 1 otherwise
   float* partial;      // split mode: partial logits, [tile][split][expert / 4][token][expert mod 4]
   int32_t plan_cpl;    // 0: no plan; 1 or 2: the one-wave planner's candidates per lane
+  int32_t arrival_polls;   // kShare: looks at the arrival word before a slice is given up
   PlanDeviceLaunch plan;   // the swap plan of the counts, made by the last workgroup
 };
 
@@ -588,10 +589,6 @@ __device__ __forceinline__ f32x4 partial_load(const __amdgpu_buffer_rsrc_t& rsrc
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, kDeviceScope));
 }
 
-// Polls of a tile's arrival word before a workgroup gives its slice to the tile's last arrival: each
-// is a trip to memory (0.2 us or more), so at least 50 us in all, several times the spread of one
-// launch's workgroups.
-constexpr int kArrivalPolls = 256;
 // Arrival word of a tile: arrivals in the low half, given-up slices (one bit per split) in the high.
 constexpr uint32_t kArrivalMask = 0xFFFFu;
 static_assert(kMaxSplits <= 16, "one given-up bit per split in the arrival word");
@@ -665,7 +662,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   const int chunk = MODE != kFused ? __builtin_amdgcn_readfirstlane((p.st_total + p.ks - 1) / p.ks) : p.st_total;
   const int64_t row0 = (int64_t)tile * BM;
   const int E = p.E;
-
+  const int polls = p.arrival_polls;               // (kShare)
   for (int i = tid; i < EPAD; i += kThreads) {
     hist[i] = 0;
     // padding experts get -inf in both, so their score is -inf without a per-element test
@@ -818,7 +815,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
         state = 1;
         marks = old >> 16;
       }
-      for (int i = 0; state == 0 && i < kArrivalPolls; ++i) {
+      for (int i = 0; state == 0 && i < polls; ++i) {
         const uint32_t v = __hip_atomic_load(&p.ws_tile[split_tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         state = (v & kArrivalMask) == (uint32_t)p.ks ? 1 : 0;
         __builtin_amdgcn_s_sleep(1);
@@ -1627,6 +1624,7 @@ int launch_cfg_bm(const PredictLaunch& a, const BatchShape& shape) {
   p.nstages = p.st_total;
   p.st_base = 0;
   p.ks = shape.ks;
+  p.arrival_polls = a.arrival_polls;
   p.partial = a.partial;
   p.plan_cpl = 0;
   if (a.plan != nullptr) {

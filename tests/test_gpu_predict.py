@@ -4,6 +4,7 @@ Small cases span several workgroup tiles and a ragged tail; the full DeepSeek-V3
 runs in the launch configuration the benchmark times (no debug outputs) and is checked through
 properties that hold at any size plus oracle recomputation of sampled tokens.
 """
+import ctypes
 import dataclasses
 import sys
 
@@ -563,6 +564,52 @@ def test_tiles_past_a_whole_round(T, H, dtype):
     one = run_gpu(li, wl, e2r, predictor=fb.Predictor(split=False), packed=True)
     if stats["mismatch"] == 0 and check_prediction(one, li, wl, e2r, label=f"one launch T={T}")["mismatch"] == 0:
         assert np.array_equal(a["counts"], one["counts"])
+
+
+# 16 splits of two and four tiles (33 stages: five splits empty), an expert count inside a 32-expert
+# block, 8 and 4 splits; past a whole round: one 128-row tile in 16 splits, 65 in two, 33 of float32
+@pytest.mark.parametrize("E,T,H,dtype", [(256, 65, 4224, "bf16"), (256, 255, 4224, "f32"), (200, 130, 4096, "bf16"),
+                                         (256, 1300, 4096, "bf16"), (256, 4000, 2048, "bf16"),
+                                         (256, 32769, 4096, "bf16"), (256, 32768 + 64 * 128 + 5, 1024, "bf16"),
+                                         (256, 32768 + 32 * 128 + 100, 528, "f32")])
+def test_slices_given_up(E, T, H, dtype):
+    """Splits that do not wait for their tile's others (no poll of the arrival word, or one) leave their
+    slices to the tile's last arrival: the same logits, selections and counts bit for bit as with the
+    usual wait, and a clean workspace header, over several calls."""
+    _say(f"[given up] E={E} T={T} H={H} {dtype}")
+    lib = fb._lib.lib()
+    usual, entry = lib.fb_predict_load_packed, lib.fb_test_predict_load_packed
+    entry.restype, entry.argtypes = usual.restype, list(usual.argtypes) + [ctypes.c_int32]
+    dt, code = (torch.bfloat16, 0) if dtype == "bf16" else (torch.float32, 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    x = torch.randn(T, H, generator=g, device="cuda").to(dt)
+    router = fb.pack_router_weight((0.02 * torch.randn(E, H, generator=g, device="cuda")).to(dt))
+    bias = 0.01 * torch.randn(E, generator=g, device="cuda")
+    e2r = (torch.arange(E, device="cuda") % 8).to(torch.int32)
+    ws = torch.zeros(fb.predict_split_workspace_bytes(T, E, H, dt), dtype=torch.uint8, device="cuda")
+    assert ws.numel() > 2048
+    k = 8
+    sc = fb.Scoring("sigmoid", k).to_c()
+
+    def call(polls):
+        out = [torch.full((E,), -7, dtype=torch.int32, device="cuda"), torch.full((8,), -7, dtype=torch.int32, device="cuda"),
+               torch.zeros(1, dtype=torch.float64, device="cuda"), torch.full((T, k), -7, dtype=torch.int32, device="cuda"),
+               torch.zeros((T, E), device="cuda")]
+        args = (x.data_ptr(), T, H, H, code, router.data.data_ptr(), router.data.numel(), E, None, bias.data_ptr(),
+                ctypes.byref(sc), e2r.data_ptr(), 8, out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(),
+                ws.data_ptr(), ws.numel(), out[3].data_ptr(), out[4].data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert (usual(*args) if polls is None else entry(*args, polls)) == 0
+        torch.cuda.synchronize()
+        assert not ws[:2048].any()
+        out[4] = out[4].view(torch.int32)
+        return out
+
+    ref = call(None)
+    assert int(ref[0].sum()) == T * k and int(ref[3].min()) >= 0
+    for polls in (0, 1, 0, 2):
+        for a, b in zip(call(polls), ref):
+            assert torch.equal(a, b), polls
 
 
 @pytest.mark.parametrize("E,k,offset", [(130, 9, 0), (256, 32, 1), (64, 6, 3), (40, 5, 0)])
