@@ -226,7 +226,7 @@ __global__ __launch_bounds__(NT, 1) void plan_general(PlanDeviceLaunch a) {
   __syncthreads();
   if (replicated) {
     if (tid == 0) sh.bad = 0;
-    check_placement<NT>(E, R, S, sh.item, sh.u.chk.cnt, sh.u.chk.ej, sh.u.chk.reps, sh.u.chk.base,
+    check_placement<NT>(tid, E, R, S, sh.item, sh.u.chk.cnt, sh.u.chk.ej, sh.u.chk.reps, sh.u.chk.base,
                         sh.u.chk.flag, sh.wsum, &sh.bad, &sh.J);
   } else {
     for (int e = tid; e < E; e += NT)
@@ -962,7 +962,7 @@ template <int RPL, int CPL>
 __global__ __launch_bounds__(64, 1) void plan_frontier_wave(PlanDeviceLaunch a) {
   constexpr int CAP = wave_cap(RPL, CPL);   // >= R * S >= E
   __shared__ __attribute__((aligned(16))) char lds[plan_wave_lds_bytes(CAP, RPL)];
-  plan_wave_body<RPL, CPL>(a, plan_wave_lds(lds, CAP, RPL));
+  plan_wave_body<RPL, CPL>(threadIdx.x, a, plan_wave_lds(lds, CAP, RPL));
 }
 
 }  // namespace

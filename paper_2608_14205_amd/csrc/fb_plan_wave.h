@@ -74,8 +74,8 @@ __device__ __forceinline__ void plan_sync() {
 // Exclusive prefix sum of v over the NT threads of the workgroup (every thread calls it; wsum holds
 // NT / 64 entries): shuffles within each wave, then the totals of the waves before.
 template <int NT>
-__device__ __forceinline__ int block_exclusive_scan(int v, int32_t* wsum) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ int block_exclusive_scan(int tid, int v, int32_t* wsum) {
+  const int lane = tid & 63, w = tid >> 6;
   int x = v;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -97,10 +97,9 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int32_t* wsum) {
 // 0 of *bad.  On return, after a barrier, reps[e] = c_e, *jmax = the largest c_e, and ej[c] =
 // (j << 12) | e for the replica in slot c (-1 for an empty or invalid slot; E <= 4096).
 template <int NT>
-__device__ __forceinline__ void check_placement(int E, int R, int S, const int32_t* vals, const int32_t* cnt,
-                                int32_t* ej, int32_t* reps, int32_t* base, int32_t* flag,
+__device__ __forceinline__ void check_placement(int tid, int E, int R, int S, const int32_t* vals,
+                                const int32_t* cnt, int32_t* ej, int32_t* reps, int32_t* base, int32_t* flag,
                                 int32_t* wsum, int32_t* bad, int32_t* jmax) {
-  const int tid = threadIdx.x;
   const int RS = R * S;
   for (int e = tid; e < E; e += NT) reps[e] = 0;
   for (int c = tid; c < RS; c += NT) flag[c] = 0;
@@ -124,7 +123,7 @@ __device__ __forceinline__ void check_placement(int E, int R, int S, const int32
   const int e0 = tid * chunk, e1 = e0 + chunk < E ? e0 + chunk : E;
   int acc = 0, jm = 1;
   for (int e = e0; e < e1; ++e) acc += reps[e];
-  acc = block_exclusive_scan<NT>(acc, wsum);
+  acc = block_exclusive_scan<NT>(tid, acc, wsum);
   for (int e = e0; e < e1; ++e) {
     base[e] = acc;
     acc += reps[e];
@@ -301,9 +300,8 @@ __device__ __forceinline__ void wave_top2_uniform(uint32_t v, uint32_t& largest,
 // Returns the number of swaps written.
 // CPL: candidates per lane (1 when S * S <= 64, else 2).
 template <int CPL>
-__device__ __forceinline__ int rounds_small(const PlanDeviceLaunch& a, uint2* slot, int32_t* part,
+__device__ __forceinline__ int rounds_small(int lane, const PlanDeviceLaunch& a, uint2* slot, int32_t* part,
                                             uint32_t& Lu, int64_t g_num, int64_t g_den) {
-  const int lane = threadIdx.x;
   const int E = a.E, R = a.R, S = a.S;
   const fb_budget bg = a.budget;
   const bool valid = lane < R;
@@ -475,7 +473,8 @@ __device__ __forceinline__ PlanWaveLds plan_wave_lds(char* mem, int CAP, int RPL
 
 // RPL: ranks per lane (R <= 64 * RPL); rank r lives in lane r % 64, register r / 64.
 // CPL: candidates per lane, 1 for S * S <= 64, 2 for S * S <= 128.
-// Runs in the first wave of its workgroup (threadIdx.x < 64); the caller's other waves take no part.
+// Runs in the first wave of its workgroup (lane: threadIdx.x, below 64); the caller's other waves take
+// no part.
 // PREPARED: the caller has already put the counts in lds.cnt, the slot table in lds.vals, under a
 // time budget the expert sizes in lds.ebytes, zeros in lds.part and the state of its short check in
 // lds.state, and, for a table that passes it, the slot entries and the rank loads in lds.slot and
@@ -484,7 +483,8 @@ __device__ __forceinline__ PlanWaveLds plan_wave_lds(char* mem, int CAP, int RPL
 // Eq. 9 on their link, admitted if it fits what is left of both ranks' and of the link's budgets,
 // and the round's best is the largest benefit / cost, then the tie key.
 template <int RPL, int CPL, bool PREPARED = false>
-__device__ __forceinline__ void plan_wave_body(const PlanDeviceLaunch& a, const PlanWaveLds& lds, int32_t node_in = 0) {
+__device__ __forceinline__ void plan_wave_body(int lane, const PlanDeviceLaunch& a, const PlanWaveLds& lds,
+                                               int32_t node_in = 0) {
   int32_t* const vals = lds.vals;      // the input tables
   int32_t* const cnt = lds.cnt;
   int32_t* const ej = lds.ej;
@@ -495,7 +495,6 @@ __device__ __forceinline__ void plan_wave_body(const PlanDeviceLaunch& a, const 
   int32_t* const part = lds.part;
   int32_t& s_bad = *lds.bad;
   int32_t& s_J = *lds.jmax;
-  const int lane = threadIdx.x;
   const int E = a.E, R = a.R, S = a.S, RS = R * S;
   const fb_budget bg = a.budget;
   const bool timed = RPL == 1 && a.timed;
@@ -538,7 +537,7 @@ __device__ __forceinline__ void plan_wave_body(const PlanDeviceLaunch& a, const 
   if (replicas) {
     // a value out of range is found again by the full check, a size out of range is not
     if (lane == 0) s_bad = 0;
-    check_placement<64>(E, R, S, vals, cnt, ej, reps, base, flag, nullptr, &s_bad, &s_J);
+    check_placement<64>(lane, E, R, S, vals, cnt, ej, reps, base, flag, nullptr, &s_bad, &s_J);
     J = s_J;
     any_bad = s_bad != 0 || __ballot(state & kPlanBad) != 0;
   } else {
@@ -598,7 +597,7 @@ __device__ __forceinline__ void plan_wave_body(const PlanDeviceLaunch& a, const 
   if constexpr (RPL == 1) {
     if (active && N < (int64_t)1 << 30 && J == 1 && !timed) {
       uint32_t Lu = (uint32_t)Lr[0];
-      ns = rounds_small<CPL>(a, slot, part, Lu, g_num, g_den);
+      ns = rounds_small<CPL>(lane, a, slot, part, Lu, g_num, g_den);
       Lr[0] = Lu;
       small_done = true;
     }

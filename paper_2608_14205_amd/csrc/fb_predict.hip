@@ -648,11 +648,11 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   __shared__ int32_t s_stray;                     // an expert on a rank that does not exist
   __shared__ int32_t s_redo;                      // float32: the parts do not serve this workgroup's values
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  const int tid0 = threadIdx.x;
+  const int lane0 = tid0 & 63;
   // wave-uniform by construction; readfirstlane keeps it (and every buffer-load offset derived
   // from it) in scalar registers
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
   const int we = wave % WE;
   const int wt = wave / WE;
   const int split_tile = MODE != kFused ? __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (uint32_t)p.ks)) : 0;
@@ -663,7 +663,7 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   const int64_t row0 = (int64_t)tile * BM;
   const int E = p.E;
   const int polls = p.arrival_polls;               // (kShare)
-  for (int i = tid; i < EPAD; i += kThreads) {
+  for (int i = tid0; i < EPAD; i += kThreads) {
     hist[i] = 0;
     // padding experts get -inf in both, so their score is -inf without a per-element test
     s_lbias[i] = i < E ? (p.logit_bias ? p.logit_bias[i] : 0.f) : -__builtin_inff();
@@ -687,12 +687,12 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
     const bool any = row0 < p.T && q.nstages > 0;
     if constexpr (BF16 || !parts_pay(EPAD)) {
       if (any)
-        contract<BF16 ? kBf16 : kExact, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem, nullptr);
+        contract<BF16 ? kBf16 : kExact, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane0, smem, nullptr);
     } else {
-      if (tid == 0) s_redo = 0;
+      if (tid0 == 0) s_redo = 0;
       if (any) {
         uint32_t odd = 0;
-        contract<kParts, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem, &odd);
+        contract<kParts, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane0, smem, &odd);
         odd &= 0xFFFFu;
         uint32_t least = ~0u;                      // of 2 |logit| - 1 as bits: zeros do not count
         float finite = 0.f;                        // NaN with any logit that is not
@@ -714,12 +714,23 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
             for (int b = 0; b < FT; ++b)
 #pragma unroll
               for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-          contract<kExact, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane, smem, nullptr);
+          contract<kExact, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane0, smem, nullptr);
         }
       }
     }
   }
   lds_barrier();
+
+  // The contraction of a 128-row tile takes every register.  In its sliced mode the thread's number, and
+  // what follows from it, is made again here rather than kept across it (it went to scratch memory, 12
+  // bytes per lane for bf16 and 20 for float32, which a first launch may have to set up).
+  int fresh = lane0;
+  if constexpr (SHARE && BM == 128) {
+    fresh = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(fresh));
+  }
+  const int lane = fresh;
+  const int tid = SHARE && BM == 128 ? wave * 64 + lane : tid0;
 
   float* S = reinterpret_cast<float*>(smem);
   // ---- split mode: exchange the partial logits ------------------------------------------------
@@ -1417,8 +1428,11 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   const int total = tid < E ? atomicExch(&p.ws_acc[tid], 0) : 0;
   if (tid == 0) atomicExch(p.ws_ticket, 0u);
   // every workgroup is past its wait once the last ticket is taken: the arrival words go back to zero
-  if constexpr (MODE != kFused)
-    for (int i = tid; i < (int)((p.tickets - p.full) / (uint32_t)p.ks); i += kThreads) atomicExch(&p.ws_tile[i], 0u);
+  if constexpr (MODE != kFused) {
+    uint32_t per_tile = (uint32_t)p.ks;
+    if constexpr (SHARE && BM == 128) asm volatile("" : "+s"(per_tile));   // (its reciprocal was kept, too)
+    for (int i = tid; i < (int)((p.tickets - p.full) / per_tile); i += kThreads) atomicExch(&p.ws_tile[i], 0u);
+  }
   constexpr size_t kPlanLds = (plan_wave_lds_bytes(wave_cap(1, 2), 1) + 15) / 16 * 16;
   static_assert(SMEM >= kPlanLds + FB_MAX_RANKS * 4, "the planner's tables and the rank loads fit");
   const PlanWaveLds pl = plan_wave_lds(smem, wave_cap(1, 2), 1);
@@ -1489,8 +1503,8 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
   if (has_plan && wave == 0) {
     // The swap plan of the counts (Alg. 1, frontier mode): the one-wave planner in this workgroup's
     // first wave, in LDS the selection no longer needs, with its tables already there.
-    if (p.plan_cpl == 1) plan_wave_body<1, 1, true>(p.plan, pl, my_node);
-    else plan_wave_body<1, 2, true>(p.plan, pl, my_node);
+    if (p.plan_cpl == 1) plan_wave_body<1, 1, true>(lane, p.plan, pl, my_node);
+    else plan_wave_body<1, 2, true>(lane, p.plan, pl, my_node);
   }
 }
 

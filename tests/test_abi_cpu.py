@@ -5,6 +5,9 @@ import ctypes
 import json
 import os
 import re
+import struct
+import subprocess
+import tempfile
 
 import numpy as np
 import pytest
@@ -45,6 +48,36 @@ def test_library_exports_every_declared_symbol():
     for name in _declared_functions():
         assert hasattr(lib, name), name
     assert set(L.SIGNATURES) == set(_declared_functions())
+
+
+def test_predictor_kernels_use_no_scratch_memory():
+    """Scratch memory is set up by the runtime at a first launch; the calls that promise to allocate
+    nothing must not need it.  Read from the metadata of the library's gfx950 code objects."""
+    readelf = "/opt/rocm/llvm/bin/llvm-readelf"
+    if not os.path.exists(readelf):
+        pytest.skip("llvm-readelf is not installed")
+    data = open(L.LIB_PATH, "rb").read()
+    scratch = {}
+    at = data.find(b"__CLANG_OFFLOAD_BUNDLE__")
+    while at >= 0:
+        entry = at + 32
+        for _ in range(struct.unpack_from("<Q", data, at + 24)[0]):
+            offset, size, length = struct.unpack_from("<QQQ", data, entry)
+            if b"gfx950" in data[entry + 24:entry + 24 + length]:
+                with tempfile.NamedTemporaryFile(suffix=".co") as f:
+                    f.write(data[at + offset:at + offset + size])
+                    f.flush()
+                    notes = subprocess.run([readelf, "--notes", f.name], capture_output=True, text=True,
+                                           check=True).stdout
+                names = re.findall(r"^    \.name:\s+(\S+)", notes, re.M)
+                sizes = re.findall(r"^    \.private_segment_fixed_size:\s+(\d+)", notes, re.M)
+                assert len(names) == len(sizes)
+                scratch.update(zip(names, map(int, sizes)))
+            entry += 24 + length
+        at = data.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 24)
+    predict = {n: v for n, v in scratch.items() if "predict_kernel" in n}
+    assert len(predict) >= 20
+    assert not [n for n, v in predict.items() if v]
 
 
 def test_struct_layouts_match_header():
