@@ -604,29 +604,18 @@ class Quality:
     hidden_cosine: Optional[float]
 
 
-_cosine_workspaces = {}
-
-
-def _cosine_workspace(device: torch.device) -> torch.Tensor:
-    key = device.index if device.index is not None else torch.cuda.current_device()
-    ws = _cosine_workspaces.get(key)
-    if ws is None:
-        n = int(L.lib().fb_cosine_workspace_bytes())
-        ws = _cosine_workspaces[key] = torch.empty(n, dtype=torch.uint8, device=device)
-    return ws
-
-
-def _row_cosine_into(out: torch.Tensor, a: torch.Tensor, b: torch.Tensor,
+def _row_cosine_into(out: torch.Tensor, ws: torch.Tensor, a: torch.Tensor, b: torch.Tensor,
                      stream: Optional[torch.cuda.Stream]) -> None:
+    """ws: fb_cosine_workspace_bytes for this call alone (or for others before and after it on its
+    stream), 16-byte aligned."""
     if a.dim() != 2 or a.shape != b.shape or a.dtype != b.dtype or a.device != b.device:
         raise ValueError("a and b must be matching 2-D tensors on one device")
     if a.stride(1) != 1 or b.stride(1) != 1:
         raise ValueError("rows must be contiguous")
     _one_gpu(a.device, a, b, out)
-    ws = _cosine_workspace(a.device)
     with torch.cuda.device(a.device):
         L.check(L.lib().fb_row_cosine_mean(_ptr(a), _ptr(b), a.shape[0], a.shape[1], a.stride(0),
-                                           b.stride(0), _dtype_code(a), _ptr(out), _ptr(ws), ws.numel(),
+                                           b.stride(0), _dtype_code(a), _ptr(out), _ptr(ws), ws.nbytes,
                                            _stream_handle(a.device, stream)), "fb_row_cosine_mean")
 
 
@@ -634,7 +623,11 @@ def row_cosine_mean(a: torch.Tensor, b: torch.Tensor,
                     stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """fb_row_cosine_mean: mean over rows of cos(a[r], b[r]) as a device float64 scalar."""
     out = torch.empty(1, dtype=torch.float64, device=a.device)
-    _row_cosine_into(out, a, b, stream)
+    # partial sums of this call alone, of the launch's own stream: calls on other streams or threads have
+    # theirs, and the block is not handed to another stream while the kernels run
+    with torch.cuda.stream(stream):
+        ws = torch.empty(int(L.lib().fb_cosine_workspace_bytes()), dtype=torch.uint8, device=a.device)
+    _row_cosine_into(out, ws, a, b, stream)
     return out
 
 
@@ -712,7 +705,10 @@ def prediction_quality(pred: Prediction, actual: Prediction, hidden_prev: Option
         raise ValueError("both passes need return_topk=True")
     # the results share one buffer, read back once: a read-back per value waited for the GPU four
     # times (a 64-expert study of 8190 tokens: 137 -> 102 us)
-    res = torch.empty(4, dtype=torch.int64, device=pred.topk.device)
+    # (the cosines' partial sums follow the results: both cosines run on one stream, one after the other)
+    buf = torch.empty(4 + int(L.lib().fb_cosine_workspace_bytes()) // 8, dtype=torch.int64,
+                      device=pred.topk.device)
+    res, ws = buf[:4], buf[4:]
     real = res.view(torch.float64)
     _topk_hits_into(res[0:1], real[1:2], pred.topk, actual.topk, None)
     pairs = [(pred.logits, actual.logits), (hidden_prev, hidden_target)]
@@ -721,7 +717,7 @@ def prediction_quality(pred: Prediction, actual: Prediction, hidden_prev: Option
         if a is None or b is None:
             continue
         if a.device == res.device:
-            _row_cosine_into(real[2 + i:3 + i], a, b, None)
+            _row_cosine_into(real[2 + i:3 + i], ws, a, b, None)
         else:                                    # on another GPU than the selections
             apart[i] = float(row_cosine_mean(a, b).item())
     got = res.cpu()

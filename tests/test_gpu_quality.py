@@ -126,3 +126,25 @@ def test_fold_reports_bad_placement():
     e2r = torch.tensor([0, 1, 5, 1], dtype=torch.int32, device="cuda")
     _, mm = fb.fold_rank_loads(counts, e2r, 2)
     assert float(mm.item()) == -1.0
+
+
+def test_cosines_on_two_streams():
+    """Calls on different streams, and with a stream argument, do not share partial sums."""
+    _say("[quality] cosines on two streams")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    a = [torch.randn(6000, 2048, generator=g, device="cuda").bfloat16() for _ in range(2)]
+    b = [(x.float() + s * torch.randn(x.shape, generator=g, device="cuda")).bfloat16() for x, s in zip(a, (0.1, 2.0))]
+    want = [float(fb.row_cosine_mean(x, y).item()) for x, y in zip(a, b)]
+    assert abs(want[0] - want[1]) > 0.1
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    got = [[], []]
+    for _ in range(50):
+        for i in range(2):
+            got[i].append(fb.row_cosine_mean(a[i], b[i], stream=streams[i]))
+            with torch.cuda.stream(streams[1 - i]):
+                got[1 - i].append(fb.row_cosine_mean(a[1 - i], b[1 - i]))
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert [float(v.item()) for v in got[i]] == [want[i]] * 100
