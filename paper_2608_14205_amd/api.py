@@ -245,7 +245,11 @@ class Predictor:
     def _reserve(self, nbytes: int, stream) -> None:
         if self.workspace is not None and self.workspace.numel() >= nbytes:
             return
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        # a block of the stream the calls run on, so that it is free there and stays theirs until they end
+        with torch.cuda.stream(stream):
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        if self.workspace is not None and stream is not None:
+            self.workspace.record_stream(stream)
         with torch.cuda.device(self.device):
             L.check(L.lib().fb_predict_workspace_init(ws.data_ptr(), nbytes,
                                                       _stream_handle(self.device, stream)),

@@ -672,6 +672,36 @@ def test_nan_scores_still_fill_the_selections(E, k, H, dtype, kind):
             assert np.array_equal(topk[rows], np.argsort(-z, axis=1, kind="stable")[:, :k])
 
 
+def test_workspace_growth_on_another_stream():
+    """A workspace that grows while its stream is still busy: the old block is not handed out to the
+    current stream, and every call's results are right."""
+    _say("[predict] workspace growth on another stream")
+    wl = dataclasses.replace(CONFIGS["qwen3"], H=1024)
+    _, e2r = contiguous_placement(wl.E, wl.R, wl.S)
+    e2r_t = torch.from_numpy(e2r).cuda()
+    lis = [make_layer(wl.with_T(T), 1) for T in (100, 3000)]
+    xs = [to_device(li.x, wl.dtype) for li in lis]
+    router = fb.pack_router_weight(to_device(lis[0].w, wl.dtype))
+    want = [fb.Predictor().predict_load(x, router, scoring_of(wl), e2r_t, wl.R).counts for x in xs]
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    pred = fb.Predictor(stream=side)
+    got, taken, old = [], [], []
+    with torch.cuda.stream(side):
+        busy = torch.randn(4096, 4096, device="cuda")
+        for _ in range(20):                          # the side stream is behind the host from here on
+            busy = busy @ busy * 1e-2
+    for x in xs:
+        got.append(pred.predict_load(x, router, scoring_of(wl), e2r_t, wl.R, stream=side).counts)
+        old.append(pred.workspace.data_ptr())
+        taken += [torch.full((old_bytes,), 255, dtype=torch.uint8, device="cuda")
+                  for old_bytes in (2048, pred.workspace.numel(), 2048)]
+    torch.cuda.synchronize()
+    assert old[0] != old[1] and not {t.data_ptr() for t in taken} & set(old)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
 def test_qwen3_layers_back_to_back():
     """Qwen3-MoE-shaped layers (every token against the oracle) and the device plan of each layer's
     counts under the config's budget against the oracle's plan.  All 48 layers run in bench.py's
