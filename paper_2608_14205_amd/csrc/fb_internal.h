@@ -57,9 +57,13 @@ constexpr size_t kWsBytes = 2048;
 static_assert(kWsTileTicketOffset + 4 * kMaxSplitTiles <= kWsBytes, "tile tickets fit the header");
 
 // Scratch of fb_predict_load_packed_noalloc: a workspace header, then room for the split mode's
-// partial logits of the largest batch that runs split on 256 CUs (tiles x splits <= 256, each 64
-// tokens x 256 experts or less: 256 * 64 * 256 * 4 bytes = 16 MiB; twice that is kept).
+// partial logits of the largest batch that runs split on 256 CUs: tiles x splits <= 256, each of at
+// most 128 tokens x 256 experts (the tiles past a whole round), which fill it exactly.  A device with
+// more CUs could ask for more; the entry point refuses such a batch.
 constexpr size_t kNoAllocPartialBytes = (size_t)32 << 20;
+constexpr int kMaxTileRows = 128;
+static_assert(kNoAllocPartialBytes == (size_t)256 * kMaxTileRows * FB_MAX_EXPERTS * sizeof(float),
+              "the scratch holds every split batch of 256 CUs");
 constexpr size_t kNoAllocScratchBytes = kWsBytes + kNoAllocPartialBytes;
 // Device address of this device's scratch (set up once per device: symbol lookup, then a fill
 // kernel on `stream` that zeroes its header).  FB_OK, FB_EDEVICE or FB_EUNSUPPORTED.

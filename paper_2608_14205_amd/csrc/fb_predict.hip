@@ -1576,6 +1576,7 @@ BatchShape shape_with(int bm, int epad, int64_t T, int st_total, int num_cus, si
 template <int EPAD>
 BatchShape batch_shape(int64_t T, int st_total, int num_cus, size_t room) {
   constexpr int BM = TileCfg<EPAD>::BM;
+  static_assert(BM <= kMaxTileRows && EPAD <= FB_MAX_EXPERTS, "a split's partials stay within the bound of the scratch");
   if constexpr (EPAD == 256) {
     // Half-height tiles when the full-height grid would leave CUs idle and the half-height one still
     // fits in a single round of workgroups: every CU then streams the weight for fewer tokens.
