@@ -540,9 +540,10 @@ def test_f32_large_and_infinite_values(E, H, T):
         assert np.array_equal(got, ref, equal_nan=True)
 
 
-# one token past a whole round (16 splits), 65 tiles past it (two splits), a round and a half in f32
+# past a whole round of 256 tiles of 128 tokens: one tile (16 splits), 65 tiles (two splits), one tile and
+# 33 tiles of float32 (two splits)
 @pytest.mark.parametrize("T,H,dtype", [(32769, 4096, "bf16"), (32768 + 64 * 128 + 5, 1024, "bf16"),
-                                       (32768 + 100, 528, "f32")])
+                                       (32768 + 100, 528, "f32"), (32768 + 33 * 128 - 60, 528, "f32")])
 def test_tiles_past_a_whole_round(T, H, dtype):
     """256-expert batches whose tiles past a whole round of workgroups run as a second launch in split
     mode: oracle parity on every token, bit-identical repeats, a clean workspace header, and the same

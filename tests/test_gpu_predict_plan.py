@@ -86,6 +86,36 @@ def test_fused_plan_matches_the_two_calls_and_the_oracle(name, T, H, R, S, B):
     _check(wl, slots, e2r, fb.Budget(B, layer_id=2), label=f"{name} T={T} R={R} S={S} B={B}")
 
 
+# 256 tiles of 128 tokens in one launch, the rest in splits in a second one, whose last workgroup plans
+@pytest.mark.parametrize("T,H,timed", [(33000, 256, False), (33000, 1024, False), (33000, 1024, True), (49152, 1024, False)])
+def test_fused_plan_of_two_launches(T, H, timed):
+    wl = dataclasses.replace(CONFIGS["dsv3"], T=T, H=H)
+    slots, e2r = contiguous_placement(wl.E, wl.R, wl.S)
+    assert (fb.predict_split_workspace_bytes(T, wl.E, H, torch.bfloat16) > 2048) == (H >= 1024)
+    cost = fb.CostModel(np.arange(wl.R) // 8, [88_000_000] * wl.E, (20_000, 50_000), (100_000, 25_000), 8_000_000)
+    li = make_layer(wl, 0)
+    x, wp = to_device(li.x, wl.dtype), fb.pack_router_weight(to_device(li.w, wl.dtype))
+    args = dict(select_bias=torch.from_numpy(li.select_bias).cuda())
+    budget, slots_t = fb.Budget(wl.budget), _t(slots)
+    pred, alone = fb.Predictor(), fb.Predictor()
+    for _ in range(2):
+        out, plan = pred.predict_plan(x, wp, scoring_of(wl), _t(e2r), slots_t, budget,
+                                      cost=cost if timed else None, **args)
+        ref = alone.predict_load(x, wp, scoring_of(wl), _t(e2r), wl.R, return_topk=True, **args)
+        ref_plan = (fb.plan_swaps_timed_device(ref.counts, slots_t, budget, cost) if timed
+                    else fb.plan_swaps_device(ref.counts, slots_t, budget))
+        assert torch.equal(out.counts, ref.counts) and torch.equal(out.rank_loads, ref.rank_loads)
+        assert out.max_mean.item() == ref.max_mean.item()
+        topk = ref.topk.cpu().numpy()
+        assert np.array_equal(ref.counts.cpu().numpy(), np.bincount(topk.ravel(), minlength=wl.E))
+        got = plan.to_host()
+        _same_plan(got, ref_plan.to_host())
+        assert got.swaps or timed
+        assert not pred.workspace[:2048].any() and not alone.workspace[:2048].any()
+    if not timed:
+        _same_plan(got, OP.plan_swaps(ref.counts.cpu().numpy().astype(np.int64), slots, budget.max_swaps))
+
+
 @pytest.mark.parametrize("name,T,R,S,mode", [
     ("dsv3", 2048, 32, 8, "full"),        # full mode: the workgroup planner after the prediction
     ("dsv3", 2048, 128, 2, "frontier"),   # 128 ranks: more than the fused planner takes

@@ -55,6 +55,25 @@ def test_noalloc_matches_the_workspace_entry_point():
         check_prediction(got, li, wl, e2r, label=f"noalloc/T={T}")
 
 
+# past a whole round of 256 tiles of 128 tokens: 128 tiles in two splits, whose partial logits fill the
+# scratch to its last byte; 86 tiles in two; one in 16
+@pytest.mark.parametrize("T,H", [(49152, 1024), (32768 + 86 * 128 - 7, 1024), (32769, 4096)])
+def test_noalloc_tiles_past_a_whole_round(T, H):
+    wl = dataclasses.replace(CONFIGS["dsv3"], T=T, H=H)
+    _, e2r = contiguous_placement(wl.E, wl.R, wl.S)
+    need = fb.predict_split_workspace_bytes(T, wl.E, H, torch.bfloat16)
+    print(f"[noalloc] T={T} H={H} workspace {need}", flush=True)
+    assert need > 2048 and (T < 49152 or need == 2048 + (32 << 20))
+    li = make_layer(wl, 1)
+    pred = fb.Predictor()
+    for _ in range(2):
+        ref, out = _run_both(wl, li, e2r, pred)
+        for name in ("counts", "rank_loads", "topk"):
+            assert torch.equal(getattr(ref, name), getattr(out, name)), name
+        assert torch.equal(ref.logits.view(torch.int32), out.logits.view(torch.int32))
+        assert int(out.counts.sum()) == T * wl.k
+
+
 def test_noalloc_empty_batch():
     wl = dataclasses.replace(CONFIGS["qwen3"], T=0, H=256)
     _, e2r = contiguous_placement(wl.E, wl.R, wl.S)
