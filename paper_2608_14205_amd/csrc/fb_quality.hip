@@ -26,11 +26,12 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 }
 
 // One token per thread: the predicted experts become a bit set, the actual ones are looked up.
-// Bound by latency at the sizes of one layer: a thread's first eight ids of both lists are fetched
-// before any is used (one trip to memory instead of one per id), and the workgroups' sums meet in
-// *hits, zeroed before the launch, with the arrivals counted above bit kHitsBits (T * k < 2^48), so
-// that the last one writes the sum and the rate with no launch of their own.  T = 8190, k = 6: 4.9 us
-// as before, the rate's launch of 1.3 us and its gap gone.
+// Bound by latency at the sizes of one layer.  The workgroups' sums meet in *hits, zeroed before the
+// launch, with the arrivals counted above bit kHitsBits (T * k < 2^48), so that the last one writes the
+// sum and the rate: this kernel takes 4.9 us at T = 8190, k = 6 as it did before, and the rate's launch
+// of 1.3 us and its gap are gone.  Ids are fetched eight at a time, the first eight of both lists before
+// any is used.  One by one / eight (both launches of a call, us): T = 8190, k = 6 5.9 / 5.7, k = 8 6.6 /
+// 7.0, T = 1000, k = 2 4.7 / 5.4, k = 32 17.3 / 12.4, T = 300000, k = 8 26.7 / 21.1.
 constexpr int kHitsBits = 48;
 constexpr int kHitsBlocks = 1024;                // arrivals stay below 2^15
 constexpr int kIds = 8;                          // ids fetched together
