@@ -27,14 +27,15 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 
 // One token per thread: the predicted experts become a bit set, the actual ones are looked up.
 // Bound by latency at the sizes of one layer.  The workgroups' sums meet in *hits, zeroed before the
-// launch, with the arrivals counted above bit kHitsBits (T * k < 2^48), so that the last one writes the
-// sum and the rate: this kernel takes 4.9 us at T = 8190, k = 6 as it did before, and the rate's launch
-// of 1.3 us and its gap are gone.  Ids are fetched eight at a time, the first eight of both lists before
-// any is used.  One by one / eight (both launches of a call, us): T = 8190, k = 6 5.9 / 5.7, k = 8 6.6 /
-// 7.0, T = 1000, k = 2 4.7 / 5.4, k = 32 17.3 / 12.4, T = 300000, k = 8 26.7 / 21.1.
+// launch; where the rate is wanted they also count arrivals above bit kHitsBits (T * k < 2^48), so that
+// the last one writes the sum and the rate with no launch of its own.  Ids are fetched four at a time,
+// the first four of both lists before any is used; the unrolled code of eight at a time costs more in
+// instruction fetches than it saves.  One by one / four / eight (both launches of a call, us): T = 8190,
+// k = 6 5.6 / 5.1 / 5.4, k = 8 6.2 / 5.9 / 6.8, T = 1000, k = 2 4.4 / 4.3 / 5.1, k = 32 16.5 / 11.1 /
+// 11.8, T = 300000, k = 8 23.9 / 21.5 / 19.9; the rate adds 0.2 to 0.7, as a launch of its own 1.5.
 constexpr int kHitsBits = 48;
 constexpr int kHitsBlocks = 1024;                // arrivals stay below 2^15
-constexpr int kIds = 8;                          // ids fetched together
+constexpr int kIds = 4;                          // ids fetched together
 __global__ __launch_bounds__(kQThreads) void hits_kernel(const int32_t* __restrict__ pred,
                                                          const int32_t* __restrict__ act, int64_t T,
                                                          int32_t k, unsigned long long* __restrict__ hits,
@@ -83,6 +84,10 @@ __global__ __launch_bounds__(kQThreads) void hits_kernel(const int32_t* __restri
   if (threadIdx.x == 0) {
     unsigned long long sum = 0;
     for (int w = 0; w < kQWaves; ++w) sum += s_part[w];
+    if (rate == nullptr) {
+      if (sum) atomicAdd(hits, sum);
+      return;
+    }
     const unsigned long long all = atomicAdd(hits, (1ull << kHitsBits) | sum) + sum;
     if ((all >> kHitsBits) == gridDim.x - 1) {
       const unsigned long long total = all & ((1ull << kHitsBits) - 1);
