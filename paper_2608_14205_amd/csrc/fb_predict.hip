@@ -1525,13 +1525,22 @@ int epad_of(int32_t E) {
 //     stages, 23.0 us with 4 of 2).
 //   * Up to 8 splits, 16 for at most four 256-expert tiles.  E = 256, H = 7168, per pass with its
 //     plan, 4 / 8 / 16 splits: T = 64 39.1 / 33.5 / 31.7 us, T = 192 38.6 / 34.0 / 32.4, T = 500
-//     38.5 / 34.4 / 35.5, T = 1237 39.7 / 39.1 / 39.6.
-int split_count(int64_t tiles, int BM, int epad, int st_total, int num_cus, size_t room) {
+//     38.5 / 34.4 / 35.5.
+//   * bf16 256-expert tiles of 64 tokens take more than 4 splits only with 32 stages or more and at most
+//     0.4 tiles per stage: the more workgroups there are, each writing and reading 64 KB of partials at
+//     the same time, the more the exchange costs, and the fewer stages, the less a shorter contraction
+//     saves.  Without a plan, 4 splits / as many as the CUs take (us): H = 7168 (56 stages), T = 1344 (21
+//     tiles) 30.7 / 30.3, T = 1600 (25) 31.1 / 32.2, T = 2048 (32) 32.2 / 37.5, T = 3200 (50) 35.9 /
+//     39.4; H = 4096 (32), T = 704 (11) 24.3 / 22.8, T = 1088 (17) 24.9 / 25.7, T = 2048 27.5 / 34.0; H =
+//     3072 (24), T = 300 (5) 21.4 / 22.2.  float32 contracts longer: H = 7168, T = 2048 89.2 / 69.3.
+int split_count(int64_t tiles, int BM, int epad, bool bf16, int st_total, int num_cus, size_t room) {
   // at most half of the CUs hold tiles, and each tile has an arrival word
   if (tiles <= 0 || tiles * 2 > num_cus || tiles > kMaxSplitTiles) return 1;
   const bool few = epad == 256 && tiles <= 4 && st_total >= 2 * kMaxSplits;
   int64_t ks = num_cus / tiles;
-  const int64_t most = few ? kMaxSplits : st_total / 4 < 8 ? st_total / 4 : 8;
+  const bool crowded = epad == 256 && bf16 && BM < kMaxTileRows && (st_total < 32 || tiles * 5 > st_total * 2);
+  const int cap = crowded ? 4 : 8;
+  const int64_t most = few ? kMaxSplits : st_total / 4 < cap ? st_total / 4 : cap;
   if (ks > most) ks = most;
   const size_t per_split = (size_t)tiles * BM * epad * sizeof(float);
   if ((size_t)ks * per_split > room) ks = (int64_t)(room / per_split);
@@ -1554,10 +1563,10 @@ struct BatchShape {
   int ks;
 };
 
-BatchShape shape_with(int bm, int epad, int64_t T, int st_total, int num_cus, size_t room) {
+BatchShape shape_with(int bm, int epad, bool bf16, int64_t T, int st_total, int num_cus, size_t room) {
   BatchShape s{bm, (T + bm - 1) / bm, 0, 1};
   if (s.tiles <= num_cus) {
-    s.ks = split_count(s.tiles, bm, epad, st_total, num_cus, room);
+    s.ks = split_count(s.tiles, bm, epad, bf16, st_total, num_cus, room);
   } else if (can_share(epad)) {
     // A 256-expert tile takes a CU (LDS and registers), so the tiles past a whole number of rounds
     // would be a round of their own on a few CUs: they follow as a launch in split mode instead, and
@@ -1565,7 +1574,7 @@ BatchShape shape_with(int bm, int epad, int64_t T, int st_total, int num_cus, si
     // their own / split launch: T = 33000 214 / 154 us, T = 36000 220 / 167, T = 40000 223 / 181, T =
     // 48000 (two splits) 229 / 210.  One kernel with both kinds of workgroups saved the second launch
     // but ran its whole tiles 8% slower (117 instead of 108 us to the end of the contraction).
-    s.ks = split_count(s.tiles % num_cus, bm, epad, st_total, num_cus, room);
+    s.ks = split_count(s.tiles % num_cus, bm, epad, bf16, st_total, num_cus, room);
     s.full = s.tiles - s.tiles % num_cus;
   }
   if (s.ks == 1) s.full = s.tiles;
@@ -1574,22 +1583,22 @@ BatchShape shape_with(int bm, int epad, int64_t T, int st_total, int num_cus, si
 
 // Shape of a batch of T tokens with rows of st_total stages and `room` bytes for partials.
 template <int EPAD>
-BatchShape batch_shape(int64_t T, int st_total, int num_cus, size_t room) {
+BatchShape batch_shape(int64_t T, bool bf16, int st_total, int num_cus, size_t room) {
   constexpr int BM = TileCfg<EPAD>::BM;
   static_assert(BM <= kMaxTileRows && EPAD <= FB_MAX_EXPERTS, "a split's partials stay within the bound of the scratch");
   if constexpr (EPAD == 256) {
     // Half-height tiles when the full-height grid would leave CUs idle and the half-height one still
     // fits in a single round of workgroups: every CU then streams the weight for fewer tokens.
-    const BatchShape h = shape_with(BM / 2, EPAD, T, st_total, num_cus, room);
+    const BatchShape h = shape_with(BM / 2, EPAD, bf16, T, st_total, num_cus, room);
     if (T > 0 && h.tiles <= num_cus) return h;
   }
-  return shape_with(BM, EPAD, T, st_total, num_cus, room);
+  return shape_with(BM, EPAD, bf16, T, st_total, num_cus, room);
 }
 
 template <int EPAD>
 size_t split_bytes_cfg(int64_t T, int32_t H, int32_t dtype, int num_cus) {
   const int st_total = (H * (dtype == FB_BF16 ? 2 : 4) + kStageRowBytes - 1) / kStageRowBytes;
-  const BatchShape s = batch_shape<EPAD>(T, st_total, num_cus, SIZE_MAX);
+  const BatchShape s = batch_shape<EPAD>(T, dtype == FB_BF16, st_total, num_cus, SIZE_MAX);
   return (size_t)(s.tiles - s.full) * s.ks * s.bm * EPAD * sizeof(float);
 }
 
@@ -1668,7 +1677,7 @@ template <bool BF16, int EPAD>
 int launch_cfg(const PredictLaunch& a) {
   constexpr int BM = TileCfg<EPAD>::BM;
   const int st_total = (a.H * (BF16 ? 2 : 4) + kStageRowBytes - 1) / kStageRowBytes;
-  const BatchShape s = batch_shape<EPAD>(a.T, st_total, a.num_cus, a.partial != nullptr ? a.partial_bytes : 0);
+  const BatchShape s = batch_shape<EPAD>(a.T, BF16, st_total, a.num_cus, a.partial != nullptr ? a.partial_bytes : 0);
   if constexpr (EPAD == 256) {
     if (s.bm == BM / 2) return launch_cfg_bm<BF16, EPAD, BM / 2>(a, s);
   }
