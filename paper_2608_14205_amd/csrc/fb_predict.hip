@@ -1551,9 +1551,14 @@ int split_count(int64_t tiles, int BM, int epad, bool bf16, int st_total, int nu
 // take longer than the exchange: 256 experts in at least four slices.  The last split finishing the
 // whole tile instead / slices (us per pass with its plan): E = 256, H = 7168, T = 4096 in 4 splits
 // 46.9 / 46.5 (float32 with selections and logits written 142 / 133), T = 6000 in 2 splits 55.8 /
-// 57.4; E = 128, H = 2048, T = 4000 in 2 splits 24.2 / 28.2; E = 64, T = 3000 19.1 / 23.6.
+// 57.4; E = 128, H = 2048, T = 4000 in 2 splits 24.2 / 28.2; E = 64, T = 3000 19.1 / 23.6.  Nor for many
+// bf16 tiles of few stages without debug outputs, where the exchange is most of what is left (no plan,
+// us): H = 4096 (32 stages), T = 2500 (40 tiles) 28.3 / 28.0, T = 3500 (55) 29.3 / 30.8, T = 4096 (64)
+// 30.1 / 32.8, with both outputs 34.9 / 34.5; H = 7168 (56), T = 3500 36.6 / 36.4.
 constexpr bool can_share(int epad) { return epad == 256; }
-bool shares(int epad, int ks) { return can_share(epad) && ks >= 4; }
+bool shares(int epad, int ks, int64_t tiles, int st_total, bool bf16, bool outputs) {
+  return can_share(epad) && ks >= 4 && (outputs || !bf16 || tiles <= 48 || st_total >= 48);
+}
 
 // Tiles of a batch: tile height, tiles, how many of them are contracted whole, and the splits of the
 // ones after those (1: there are none).
@@ -1657,16 +1662,17 @@ int launch_cfg_bm(const PredictLaunch& a, const BatchShape& shape) {
   }
   hipStream_t st = static_cast<hipStream_t>(a.stream);
   const dim3 block(kThreads), split_grid((unsigned)split_blocks);
+  const bool share = shares(EPAD, p.ks, shape.tiles, p.st_total, BF16, p.topk_idx != nullptr || p.logits != nullptr);
   if (full_blocks > 0)
     hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kFused>), dim3((unsigned)full_blocks), block, 0, st, p);
   if (split_blocks > 0) {
     if constexpr (can_share(EPAD)) {
       // (full-height tiles split only past whole rounds)
-      if (shares(EPAD, p.ks) || BM == TileCfg<EPAD>::BM)
+      if (share || BM == TileCfg<EPAD>::BM)
         hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kShare>), split_grid, block, 0, st, p);
     }
     if constexpr (!can_share(EPAD) || BM != TileCfg<EPAD>::BM) {
-      if (!shares(EPAD, p.ks))
+      if (!share)
         hipLaunchKernelGGL((predict_kernel<BF16, EPAD, BM, kSplit>), split_grid, block, 0, st, p);
     }
   }

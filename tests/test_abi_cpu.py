@@ -679,6 +679,15 @@ def test_split_workspace_sizes_without_gpu():
     assert lib.fb_predict_split_workspace_bytes(77, 16, 1024, 1) == 2048 + 1 * 4 * 128 * 32 * 4
 
 
+@pytest.mark.parametrize("T,H,dtype,tiles,splits", [
+    (256, 7168, 0, 4, 16), (257, 7168, 0, 5, 8), (1408, 7168, 0, 22, 8), (1409, 7168, 0, 23, 4),
+    (1409, 7168, 1, 23, 8), (768, 4096, 0, 12, 8), (769, 4096, 0, 13, 4), (300, 3072, 0, 5, 4), (4096, 7168, 1, 64, 4),
+    (8192, 7168, 0, 128, 2), (8193, 7168, 0, 129, 0)])
+def test_split_counts_without_gpu(T, H, dtype, tiles, splits):
+    # 256 experts on 256 CUs, 64-token tiles, at the lines between the split counts (0: fused)
+    assert fb.lib().fb_predict_split_workspace_bytes(T, 256, H, dtype) == 2048 + tiles * splits * 64 * 256 * 4
+
+
 def test_bindings_refuse_host_tensors():
     """Every binding that launches a kernel refuses tensors that do not live on a GPU before
     anything reaches the library: a host pointer would be dereferenced by the kernel."""

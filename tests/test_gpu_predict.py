@@ -673,6 +673,21 @@ def test_nan_scores_still_fill_the_selections(E, k, H, dtype, kind):
             assert np.array_equal(topk[rows], np.argsort(-z, axis=1, kind="stable")[:, :k])
 
 
+@pytest.mark.parametrize("T,H,dtype", [(3072, 2048, "bf16"), (3073, 2048, "bf16"), (4090, 4096, "bf16"), (3500, 1024, "f32")])
+def test_finish_with_and_without_outputs(T, H, dtype):
+    """Four splits of up to and past 48 tiles: finished in slices when outputs are asked for, by one split
+    otherwise (bf16 past 48 tiles).  Both add the same partials in the same order, so the counts agree."""
+    _say(f"[finish] T={T} H={H} {dtype}")
+    wl = dataclasses.replace(CONFIGS["dsv3"].with_T(T), H=H, dtype=dtype)
+    _, e2r = contiguous_placement(wl.E, wl.R, wl.S)
+    li = make_layer(wl, 1)
+    a = run_gpu(li, wl, e2r, packed=True)
+    check_prediction(a, li, wl, e2r, label=f"finish T={T}")
+    check_counts_consistent(a, wl, e2r)
+    b = run_gpu(li, wl, e2r, packed=True, debug=False)
+    assert np.array_equal(a["counts"], b["counts"]) and np.array_equal(a["rank_loads"], b["rank_loads"])
+
+
 def test_workspace_growth_on_another_stream():
     """A workspace that grows while its stream is still busy: the old block is not handed out to the
     current stream, and every call's results are right."""
