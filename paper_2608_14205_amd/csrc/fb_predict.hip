@@ -596,12 +596,13 @@ static_assert(kMaxSplits <= 16, "one given-up bit per split in the arrival word"
 // Whether float32 inputs are contracted in parts.  Float32 matrix instructions / parts (us per packed
 // call): E = 8, H = 4096, T = 1000 20.9 / 21.9; E = 64, H = 2048, T = 1000 19.6 / 20.4, T = 30000 96.0 /
 // 104.8; E = 128, H = 2048, T = 1000 27.2 / 26.0, T = 20000 150.5 / 132.2; E = 256, H = 7168, T = 64
-// 43.7 / 35.1, T = 4096 with selections and logits 133 / 105, T = 20000 866 / 463.
+// 43.7 / 35.1, T = 4096 with selections and logits 132 / 106, T = 20000 866 / 463.
 constexpr bool parts_pay(int epad) { return epad >= 128; }
 // The parts serve a workgroup whose values are all sums of their parts and whose logits are zero or at
 // least 2^-100 (below, part products would underflow that a float32 product keeps) and finite.  Any
 // other workgroup (infinities and values next to the largest among them, as both parts of such a value
-// are infinite or NaN) contracts again on the float32 matrix instructions and has their results.
+// are infinite or NaN) contracts again on the float32 matrix instructions and has their results (E =
+// 256, T = 4096: 116 us, 225 when every workgroup does).
 // kLeastLogit: 2^-100, doubled, as bits, less one.
 constexpr uint32_t kLeastLogit = (27u << 24) - 1u;
 
