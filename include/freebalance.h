@@ -209,7 +209,7 @@ int fb_pack_router_weight(const void* router_w, int32_t E, int32_t H, int32_t dt
  * NaN scores gets k distinct experts, which ones and in which order is not specified.
  * Logits are accumulated in float32.  FB_BF16 products are exact; FB_F32 products are float32 ones for
  * up to 64 experts, and with more experts sums of the products of three bf16 parts of each value, which
- * leave out less than 2^-24 of a product (inputs outside the range in which the parts hold every value,
+ * leave out at most 2^-23.9 of a product (inputs outside the range in which the parts hold every value,
  * and logits that are not finite or below 2^-100, are computed from float32 products there too). */
 int fb_predict_load(const void* hidden, int64_t T, int32_t H, int64_t ld_hidden, int32_t dtype,
                     const void* router_w, int32_t E, const float* logit_bias,
