@@ -292,6 +292,12 @@ __global__ void pack_kernel(const char* __restrict__ w, int32_t E, int32_t Hbyte
   }
 }
 
+// Whether float32 inputs are contracted in parts.  Float32 matrix instructions / parts (us per packed
+// call): E = 8, H = 4096, T = 1000 20.9 / 21.9; E = 64, H = 2048, T = 1000 19.6 / 20.4, T = 30000 96.0 /
+// 104.8; E = 128, H = 2048, T = 1000 27.2 / 26.0, T = 20000 150.5 / 132.2; E = 256, H = 7168, T = 64
+// 43.7 / 35.1, T = 4096 with selections and logits 132 / 106, T = 20000 866 / 463.
+constexpr bool parts_pay(int epad) { return epad >= 128; }
+
 // ---- the contraction ---------------------------------------------------------------------------
 // acc[fe][ft] += (router weight block fe) x (hidden block ft) over every stage of the tile; the NS
 // stage buffers start at ring_lds.  MATH: bf16 inputs, float32 inputs in bf16 parts, or float32 inputs
@@ -402,6 +408,20 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
     for (int ft = 0; ft < FT; ++ft) ds_read_b128(dst[ft], a, ft * 32 * kStageRowBytes);
   };
 
+  // Where float32 inputs always come this way, every other k-pair goes to a second sum, added at the end,
+  // so that each is rounded half as often.  Error of the logits against 64 bits, of their norm, one sum /
+  // parts / two sums: E = 64, H = 2048 3.9e-7 / 2.4e-7 / 2.0e-7, E = 8, H = 4096 4.0e-7 / 2.3e-7 / 1.9e-7.
+  // Time is the same (E = 64, T = 1000 19.6 / 19.7 us with one / two).
+  constexpr bool kTwoSums = MATH == kExact && !parts_pay(EPAD);
+  f32x16 odd_sum[FE][FT];
+  if constexpr (kTwoSums) {
+#pragma unroll
+    for (int a = 0; a < FE; ++a)
+#pragma unroll
+      for (int b = 0; b < FT; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) odd_sum[a][b][r] = 0.f;
+  }
   auto mma = [&](const u32x4(&a)[FE], const u32x4(&b)[FT]) {
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft)
@@ -415,8 +435,10 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
           const f32x4 av = __builtin_bit_cast(f32x4, a[fe]);
           const f32x4 bv = __builtin_bit_cast(f32x4, b[ft]);
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[fe][ft] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc[fe][ft], 0, 0, 0);
+          for (int j = 0; j < 4; ++j) {
+            f32x16& to = kTwoSums && (j & 1) ? odd_sum[fe][ft] : acc[fe][ft];
+            to = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], to, 0, 0, 0);
+          }
         }
       }
   };
@@ -560,6 +582,14 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[FE][FT], const Params& p,
   for (int i = 0; i < kRingW; ++i) pin_acc(ring[i]);
   pin(bq[0]);
   pin(bq[1]);
+  if constexpr (kTwoSums) {
+#pragma unroll
+    for (int a = 0; a < FE; ++a)
+#pragma unroll
+      for (int b = 0; b < FT; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][b][r] += odd_sum[a][b][r];
+  }
   if constexpr (MATH == kParts) {                // the last pair of k-steps
     mma_parts(sa[1], sb[1], 0);
     mma_parts(sa[1], sb[1], 1);
@@ -593,11 +623,6 @@ __device__ __forceinline__ f32x4 partial_load(const __amdgpu_buffer_rsrc_t& rsrc
 constexpr uint32_t kArrivalMask = 0xFFFFu;
 static_assert(kMaxSplits <= 16, "one given-up bit per split in the arrival word");
 
-// Whether float32 inputs are contracted in parts.  Float32 matrix instructions / parts (us per packed
-// call): E = 8, H = 4096, T = 1000 20.9 / 21.9; E = 64, H = 2048, T = 1000 19.6 / 20.4, T = 30000 96.0 /
-// 104.8; E = 128, H = 2048, T = 1000 27.2 / 26.0, T = 20000 150.5 / 132.2; E = 256, H = 7168, T = 64
-// 43.7 / 35.1, T = 4096 with selections and logits 132 / 106, T = 20000 866 / 463.
-constexpr bool parts_pay(int epad) { return epad >= 128; }
 // The parts serve a workgroup whose values are all sums of their parts and whose logits are zero or at
 // least 2^-100 (below, part products would underflow that a float32 product keeps) and finite.  Any
 // other workgroup (infinities and values next to the largest among them, as both parts of such a value
@@ -716,11 +741,14 @@ __global__ __launch_bounds__(kThreads, 1) void predict_kernel(Params p) {
 #pragma unroll
               for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
           contract<kExact, EPAD, FE, FT, NS, BM, TW>(acc, q, row0, wave, we, wt, lane0, smem, nullptr);
+          lds_barrier();
         }
+      } else {
+        lds_barrier();
       }
     }
   }
-  lds_barrier();
+  if constexpr (BF16 || !parts_pay(EPAD)) lds_barrier();   // (parts: behind the flag above)
 
   // The contraction of a 128-row tile takes every register.  In its sliced mode the thread's number, and
   // what follows from it, is made again here rather than kept across it (it went to scratch memory, 12
